@@ -165,7 +165,8 @@ int alif_refractory_steps(double dt_ms, double arp_ms);
  * 256-byte aligned. */
 int alif_carry_bytes(const alif_desc *desc, size_t *bytes);
 
-/* Bytes of device scratch alif_backward needs (per-(b, neuron) FP64 partial sums). */
+/* Bytes of device scratch alif_backward needs (per-(b, neuron) FP64 partial sums, of each
+ * time chunk where a call wants no input-current gradient). */
 int alif_backward_workspace_bytes(const alif_desc *desc, size_t *bytes);
 
 /* ---- compute ----------------------------------------------------------------- */
@@ -327,7 +328,8 @@ int alif_backward(const alif_desc *desc, const alif_params *prm,
  * For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving or training loops, harnesses that forbid hipMalloc): the same
  * backward as alif_backward, same arguments and results, without the workspace
- * argument. Its scratch (the FP64 partial sums, 40 bytes per (b, neuron), plus the
+ * argument. Its scratch (the FP64 partial sums, 40 bytes per (b, neuron), and 96 per time
+ * chunk where the call is cut into chunks that fit, plus the
  * weight-gradient GEMM's split-K tiles when grad_W is requested for spike input)
  * lives in a static device array of ALIF_NOALLOC_SCRATCH_BYTES inside the library,
  * one per device, held until the process ends. This call allocates nothing: no

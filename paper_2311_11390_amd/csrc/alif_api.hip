@@ -192,7 +192,7 @@ int set_error(int code, const char *msg) { return fail(code, "%s", msg); }
 // for the input gradient, then the input-current gradient as bfloat16 [B][T][N] for
 // a call that passes no grad_current.
 struct BwdWs {
-    size_t part, gemm, wgev, wt, gi16, total;
+    size_t part, gemm, wgev, wt, gi16, gi16_end, total;
 };
 BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
     BwdWs w;
@@ -202,7 +202,13 @@ BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
     w.wt = w.wgev + (p.spikes_in ? align256(wgrad_event_bytes(p.B, p.T, p.n_in, p.N)) : 0);
     const bool bf = p.spikes_in && desc->gemm_precision == ALIF_GEMM_BF16;
     w.gi16 = w.wt + (bf ? align256(gemm_wbf16_bytes(p.N, p.n_in)) : 0);
-    w.total = w.gi16 + (bf ? align256((size_t)p.B * p.T * p.N * 2) : 0);
+    w.total = w.gi16_end = w.gi16 + (bf ? align256((size_t)p.B * p.T * p.N * 2) : 0);
+    // a call without an input-current gradient uses none of the regions behind the partial
+    // sums, which it may keep for several time chunks
+    if (desc->algo == ALIF_ALGO_BLOCKS) {
+        const size_t st = bwd_stream_bytes(p.B, p.N, bwd_stream_chunks(p.B, p.T, p.N, p.TR, SIZE_MAX));
+        w.total = w.total > st ? w.total : st;
+    }
     return w;
 }
 // Whether a backward call keeps the input-current gradient as bfloat16 in its
@@ -210,6 +216,11 @@ BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
 // the projections' gradients asked for and no grad_current to fill. N % 8 == 0
 // keeps the bfloat16 rows 16-byte aligned, so the GEMMs take the same kernels as
 // from a float gI (and give the same bits).
+// Whether a backward call wants no input-current gradient in any form, so that the
+// streaming backward takes it (detached block backward).
+bool bwd_streams(const alif_desc *desc, bool grad_current, bool gi16) {
+    return desc->algo == ALIF_ALGO_BLOCKS && desc->grad_policy != ALIF_GRAD_ATTACHED && !grad_current && !gi16;
+}
 bool bwd_gi16(const alif_desc *desc, const Prob &p, bool grad_current, bool grad_vt, bool proj) {
     return p.spikes_in && desc->gemm_precision == ALIF_GEMM_BF16 && desc->algo == ALIF_ALGO_BLOCKS &&
            desc->grad_policy != ALIF_GRAD_ATTACHED && !grad_vt && proj && !grad_current && p.N % 8 == 0;
@@ -408,12 +419,15 @@ int alif_forward(const alif_desc *desc, const alif_params *prm, const void *inpu
     return ALIF_OK;
 }
 
-int alif_backward(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
-                  const float *current, const void *carries, const float *grad_spikes,
-                  const float *grad_v, const float *grad_theta, float *grad_current,
-                  float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
-                  float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
-                  void *stream) {
+}  // extern "C"
+
+// alif_backward with at most max_bytes for the partial sums of the streaming backward.
+static int backward_impl(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
+                         const float *current, const void *carries, const float *grad_spikes,
+                         const float *grad_v, const float *grad_theta, float *grad_current,
+                         float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
+                         float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
+                         void *stream, size_t max_bytes) {
     Prob p;
     int rc = check_desc(desc, &p);
     if (rc) return rc;
@@ -473,7 +487,12 @@ int alif_backward(const alif_desc *desc, const alif_params *prm, const void *inp
         a.gI = grad_current;
         a.gI16 = gi16 ? reinterpret_cast<uint16_t *>((char *)workspace + bwd_ws_layout(desc, p).gi16) : nullptr;
         a.part = part;
-        e = launch_blocks_bwd(a, st);
+        if (bwd_streams(desc, grad_current != nullptr, gi16)) {
+            a.chunks = bwd_stream_chunks(p.B, p.T, p.N, p.TR, max_bytes);
+            e = launch_bwd_stream(a, st);
+        } else {
+            e = launch_blocks_bwd(a, st);
+        }
         if (e != hipSuccess) return hip_fail(e, "block backward launch");
     } else {
         SeqArgs a{};
@@ -531,6 +550,19 @@ int alif_backward(const alif_desc *desc, const alif_params *prm, const void *inp
     return ALIF_OK;
 }
 
+extern "C" {
+
+int alif_backward(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
+                  const float *current, const void *carries, const float *grad_spikes,
+                  const float *grad_v, const float *grad_theta, float *grad_current,
+                  float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
+                  float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
+                  void *stream) {
+    return backward_impl(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
+                         grad_input, grad_W, grad_bias, grad_tau_mem, grad_tau_adapt, grad_d, grad_theta0,
+                         workspace, stream, SIZE_MAX);
+}
+
 int alif_backward_noalloc(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
                           const float *current, const void *carries, const float *grad_spikes,
                           const float *grad_v, const float *grad_theta, float *grad_current,
@@ -545,7 +577,7 @@ int alif_backward_noalloc(const alif_desc *desc, const alif_params *prm, const v
     const BwdWs lay = bwd_ws_layout(desc, p);
     size_t need = grad_W ? lay.wt : lay.gemm;
     if (grad_input && lay.gi16 > lay.wt) need = lay.gi16;   // W transposed and rounded
-    if (bwd_gi16(desc, p, grad_current != nullptr, grad_v || grad_theta, grad_W || grad_input)) need = lay.total;
+    if (bwd_gi16(desc, p, grad_current != nullptr, grad_v || grad_theta, grad_W || grad_input)) need = lay.gi16_end;
     if (need > (size_t)ALIF_NOALLOC_SCRATCH_BYTES)
         return fail(ALIF_EUNSUPPORTED,
                     "alif_backward_noalloc: this problem needs %zu bytes of scratch, more than the %u-byte "
@@ -555,9 +587,10 @@ int alif_backward_noalloc(const alif_desc *desc, const alif_params *prm, const v
     if ((rc = noalloc_scratch(&ws))) return rc;
     // every scratch byte the kernels read they have written earlier in the same call
     // (the partial sums of every (b, neuron), every split's tile), so nothing is cleared
-    return alif_backward(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
+    // (the streaming backward takes one chunk where more would not fit the array)
+    return backward_impl(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
                          grad_input, grad_W, grad_bias, grad_tau_mem, grad_tau_adapt, grad_d, grad_theta0, ws,
-                         stream);
+                         stream, ALIF_NOALLOC_SCRATCH_BYTES);
 }
 
 // ---------------------------------------------------------------------------

@@ -835,7 +835,7 @@ __global__ __launch_bounds__(Geo<SEG>::THREADS) void k_blocks_bwd(BwdArgs a) {
                     if (k == 0) lA0 = lA;
                     else qp = fmaf(c.pt[k > 0 ? k - 1 : 0], lA, qp);
                     pth += lt[k];
-                    if constexpr (GI != 0) st_gi<GI>(rGI, c.off(k, bo), c.omb * lV);
+                    st_gi<GI>(rGI, c.off(k, bo), c.omb * lV);
                 }
                 pb = fmaf(-bias, slV, pb);
                 pp = c.dd * fmaf(a1, qp, aprev0 * lA0);
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(Geo<SEG>::THREADS) void k_blocks_bwd(BwdArgs a) {
                     pdd = fmaf(ak[k], lt[k], pdd);
                     pth += lt[k];
                     sglV += glV;
-                    if constexpr (GI != 0) st_gi<GI>(rGI, c.off(k, bo), c.omb * glV);
+                    st_gi<GI>(rGI, c.off(k, bo), c.omb * glV);
                 }
                 pp *= c.dd;
                 pbias = c.omb * sglV;
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(Geo<SEG>::THREADS) void k_blocks_bwd(BwdArgs a) {
                     if (k == 0) lA0 = lA;
                     else qp = fmaf(c.pt[k > 0 ? k - 1 : 0], lA, qp);
                     pth += ltk;
-                    if constexpr (GI != 0) st_gi<GI>(rGI, c.off(k, bo), c.omb * lV);
+                    st_gi<GI>(rGI, c.off(k, bo), c.omb * lV);
                 }
                 pb = fmaf(-bias, slV, pb);
                 pp = c.dd * fmaf(a1, qp, aprev0 * lA0);
@@ -948,7 +948,7 @@ __global__ __launch_bounds__(Geo<SEG>::THREADS) void k_blocks_bwd(BwdArgs a) {
                     pdd = fmaf(ak_c, ltk, pdd);
                     pth += ltk;
                     sglV += glV;
-                    if constexpr (GI != 0) st_gi<GI>(rGI, c.off(k, bo), c.omb * glV);
+                    st_gi<GI>(rGI, c.off(k, bo), c.omb * glV);
                     ak_c = aprev;
                 }
                 pp *= c.dd;
@@ -1398,7 +1398,7 @@ hipError_t blocks_bwd_launch(const BwdArgs &a, hipStream_t st) {
     }
     const size_t sm = bwd_smem_bytes<SEG, L>(a.TR);
     const bool gvt = a.gV || a.gTH;
-    const int gi = a.gI ? 1 : (a.gI16 ? 2 : 0);   // (a bfloat16 gI comes without gV / gTH)
+    if (!a.gI && (gvt || !a.gI16)) return hipErrorInvalidValue;   // (a bfloat16 gI comes without gV / gTH)
 #define ALIF_LB3(G1, G2, SG)                                                                      \
     do {                                                                                          \
         if (a.TR == SEG * L)                                                                      \
@@ -1414,8 +1414,9 @@ hipError_t blocks_bwd_launch(const BwdArgs &a, hipStream_t st) {
         else if (a.surrogate == 2) ALIF_LB3(G1, G2, 2);                                           \
         else ALIF_LB3(G1, G2, 0);                                                                 \
     } while (0)
-    if (gvt) { if (gi == 1) ALIF_LB(true, 1); else ALIF_LB(true, 0); }
-    else { if (gi == 1) ALIF_LB(false, 1); else if (gi == 2) ALIF_LB(false, 2); else ALIF_LB(false, 0); }
+    if (gvt) ALIF_LB(true, 1);
+    else if (a.gI) ALIF_LB(false, 1);
+    else ALIF_LB(false, 2);
 #undef ALIF_LB
 #undef ALIF_LB3
     return hipGetLastError();

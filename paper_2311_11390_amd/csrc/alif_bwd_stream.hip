@@ -1,0 +1,334 @@
+// Parameter-gradient backward without an input-current gradient (the fits: the
+// gradients of tau_mem, tau_adapt, d, theta0 and bias alone), as one pass forward
+// in time over independent time chunks.
+//
+// The sums the reverse adjoint collects,
+//   dbeta = sum_t src[t] W[t],   dbias = sum_t src[t] U[t],
+//   dp = d sum_t lt[t] Q[t],     dd = sum_t lt[t] a[t],   dtheta0 = sum_t lt[t],
+// with src = dL/dV + dL/dS s'(V - theta), lt = dL/dtheta - dL/dS s'(V - theta), are
+// inner products of the same local terms with the sensitivities W = dV/dbeta,
+// U = dV/dbias and Q = da/dp, which run forward beside the membrane (detached
+// policy: the reset, the adaptation jump and the gate are constants):
+//   V[t] = (beta V[t-1] + (1 - beta) gate I) (1 - S[t-1]),  a[t] = p a[t-1] + S[t-1],
+//   W[t] = (beta W[t-1] + V[t-1] - gate I) (1 - S[t-1]),
+//   U[t] = (beta U[t-1] + (1 - beta) gate) (1 - S[t-1]),    Q[t] = p Q[t-1] + a[t-1].
+// So nothing has to be kept for a reverse pass, any T_R streams through the same
+// registers, and a row's T steps can be cut anywhere: each chunk starts from the V
+// and a the forward saved at its first block, with W = U = Q = 0, and also sums
+//   CB = sum src pv,  CA = sum lt pa,  pv = prod beta (1 - S),  pa = p^steps,
+// the weights its sums have on the W, U and Q that reach it; k_join_chunks joins the
+// chunks in time order. Spike steps come from the saved carries, as in the block
+// backward; the state between them is recomputed here.
+//
+// Everything but the surrogate is FP64: on this machine an FP64 multiply-add issues at
+// the rate of an FP32 one (no packed FP32 here), and per-step FP32 decays over a chunk
+// would lose what a block's rounded powers keep.
+//
+// What bounds it: HBM. A quiet step is 26 vector instructions and no barrier or LDS (the
+// block backward issues 51 and stitches segments behind a barrier a block, on one
+// wave-group per 64 neurons whatever T is). Against that kernel, us a call with the join
+// and the batch sum: 64 x 256 x 20000, T_R 40: 611 -> 524 (5.0 TB/s); 4 x 2048 x 20000,
+// T_R 20: 888 -> 268 (4.9 TB/s); 8 x 600 x 10000, T_R 100: 606 -> 124; 16 x 256 x 2000,
+// T_R 2: 349 -> 44.
+#include "alif_common.h"
+#include "alif_kernels.h"
+
+namespace alif {
+namespace {
+
+constexpr int ST_WAVES = 4;   // waves (work items) a workgroup
+constexpr int ST_FAR = 1 << 30;
+// Waves the chunks aim at. Against 1024 / 2048 / 4096 / 8192 waves, 3072 (three a SIMD)
+// measured 524 us on 64 x 256 x 20000 steps at T_R 40 (595 / 540 / 544 / 569: below, too
+// little in flight; above, more streams over memory and more sums to join) and 268 us on
+// 4 x 2048 x 20000 at T_R 20 (354 / 278 / 282 / 310).
+constexpr int ST_TARGET_WAVES = 3072;
+constexpr int ST_MIN_STEPS = 64;   // a chunk's set-up (five exponentials, a first load) is worth about 16 steps
+constexpr int ST_RING = 2;         // groups of steps in registers; 3 measured the same
+
+// KS: steps loaded and processed together; TRS: T_R where a group of KS steps holds
+// whole blocks of TRS steps, 0: a block of T_R >= KS steps in ceil(T_R / KS) groups,
+// the last one partial.
+template <int KS, int TRS, bool GVT, int SG>
+__global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
+    constexpr int M = TRS > 0 ? KS / TRS : 1;   // blocks a group
+    constexpr int RING = ST_RING;               // groups in registers
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int item = xcd_remap(blockIdx.x, gridDim.x) * ST_WAVES + wave;
+    // neuron groups fastest: a workgroup's waves read neighbouring columns of the same rows
+    const int bc = item / a.n_groups, g = item - bc * a.n_groups;
+    const int b = bc / a.chunks, ch = bc - b * a.chunks;
+    if (b >= a.B) return;   // no barrier in this kernel
+    const int N = a.N, TR = TRS > 0 ? TRS : a.TR;
+    const int n = g * 64 + lane, nc = min(n, N - 1);
+    const int blk0 = ch * a.nbc, blk1 = min(a.NB, blk0 + a.nbc);
+    const int tend = min(a.T, blk1 * TR);
+
+    const double dt = a.dt, tm = a.tau_m[nc], ta = a.tau_a[nc];
+    const double beta = exp(-dt / tm), omb = -expm1(-dt / tm), p = exp(-dt / ta);
+    const double dd = a.d[nc], th0 = a.theta0[nc], bias = a.bias_k ? a.bias_k[nc] : 0.0;
+    const double ob = omb * bias;
+
+    const size_t TN = (size_t)a.T * N, CN = (size_t)(a.NB + 1) * N;
+    // an absent gradient reads the input's rows instead and is zeroed at its use (without
+    // dL/dV and dL/dtheta, an absent dL/dS leaves nothing to sum)
+    const float *I = a.I + b * TN;
+    const bool hasS = a.gS != nullptr, hasV = GVT && a.gV != nullptr, hasT = GVT && a.gTH != nullptr;
+    const float *gS = hasS ? a.gS + b * TN : I, *gV = hasV ? a.gV + b * TN : I, *gT = hasT ? a.gTH + b * TN : I;
+    const uint8_t *cts = a.ck.ts + b * CN;
+
+    double V = a.ck.v[b * CN + (size_t)blk0 * N + nc], av = a.ck.a[b * CN + (size_t)blk0 * N + nc];
+    const int ts_in = min((int)cts[(size_t)blk0 * N + nc], TR);
+    int tl = ts_in > 0 ? (blk0 - 1) * TR + ts_in - 1 : -ST_FAR;   // last spike before the step
+    double W = 0.0, U = 0.0, Q = 0.0, pv = 1.0, pa = 1.0;
+    double sb = 0.0, sbias = 0.0, sp = 0.0, sd = 0.0, sth = 0.0, CB = 0.0, CA = 0.0;
+
+    struct Slot {
+        float x[KS], gs[KS], gv[GVT ? KS : 1], gt[GVT ? KS : 1];
+        int ts[M];
+    };
+    // group q of the chunk: blocks [blk, blk + M), steps from t (all uniform)
+    const int gpb = TRS > 0 ? 1 : (TR + KS - 1) / KS;
+    const int groups = !GVT && !hasS ? 0 : TRS > 0 ? (blk1 - blk0 + M - 1) / M : (blk1 - blk0) * gpb;
+    struct Pos {
+        int blk, j;
+    };
+    auto step0 = [&](Pos q) { return TRS > 0 ? q.blk * TR : q.blk * TR + q.j * KS; };
+    auto next = [&](Pos q) {
+        if constexpr (TRS > 0) return Pos{q.blk + M, 0};
+        else return q.j + 1 < gpb ? Pos{q.blk, q.j + 1} : Pos{q.blk + 1, 0};
+    };
+    // rows past the chunk's end are read from its last row (and not used)
+    // Every access is in range (rows and lanes are clamped), so the row goes into the
+    // scalar offset, which the buffer's range check leaves out.
+    const uint32_t n4 = (uint32_t)nc * 4u;
+    const rsrc_t rI = make_rsrc(I, (uint32_t)(TN * 4)), rS = make_rsrc(gS, (uint32_t)(TN * 4));
+    const rsrc_t rV = make_rsrc(gV, (uint32_t)(TN * 4)), rT = make_rsrc(gT, (uint32_t)(TN * 4));
+    const rsrc_t rC = make_rsrc(cts, (uint32_t)CN);
+    auto ldf = [&](rsrc_t r, uint32_t row) __attribute__((always_inline)) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, n4, row, 0));
+    };
+    auto load = [&](Slot &s, Pos q) __attribute__((always_inline)) {
+        const int t = step0(q);
+#pragma unroll
+        for (int k = 0; k < KS; k++) {
+            const uint32_t r = (uint32_t)(min(t + k, tend - 1) * N) * 4u;
+            s.x[k] = ldf(rI, r);
+            s.gs[k] = ldf(rS, r);
+            if constexpr (GVT) {
+                s.gv[k] = ldf(rV, r);
+                s.gt[k] = ldf(rT, r);
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < M; m++) s.ts[m] = __builtin_amdgcn_raw_buffer_load_b8(rC, nc, (min(q.blk + m, blk1 - 1) + 1) * N, 0);
+    };
+
+    // the local terms of a step, once V, a and the sensitivities are its own
+    auto collect = [&](const Slot &s, int k) __attribute__((always_inline)) {
+        const double u = V - fma(dd, av, th0);
+        const float gs = !GVT || hasS ? s.gs[k] : 0.0f;
+        const double q = (double)(gs * surrogate_grad<SG>((float)u, a.slope));
+        double src = q, lt = -q;
+        if constexpr (GVT) {
+            src = hasV ? (double)s.gv[k] + q : q;
+            lt = hasT ? (double)s.gt[k] - q : -q;
+        }
+        sb = fma(src, W, sb);
+        sbias = fma(src, U, sbias);
+        sp = fma(lt, Q, sp);
+        sd = fma(lt, av, sd);
+        sth += lt;
+        CB = fma(src, pv, CB);
+        CA = fma(lt, pa, CA);
+    };
+    auto group = [&](Slot &s, Pos q) __attribute__((always_inline)) {
+        const int t0 = step0(q);
+        int nv = min(KS, tend - t0);
+        if constexpr (TRS == 0) nv = min(nv, TR - q.j * KS);
+        int tc[M];   // this block's spike step, ST_FAR if none
+        bool act = t0 - tl < TR;
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            tc[m] = s.ts[m] > 0 ? (q.blk + m) * TR + min(s.ts[m], TR) - 1 : ST_FAR;
+            act |= tc[m] < t0 + KS - 1;
+        }
+        if (nv == KS && !__any(act)) {   // no lane has a reset, a mask or a jump in this group
+#pragma unroll
+            for (int k = 0; k < KS; k++) {
+                const double x = s.x[k];
+                W = fma(beta, W, V - (x + bias));
+                V = fma(beta, V, fma(omb, x, ob));
+                U = fma(beta, U, omb);
+                Q = fma(p, Q, av);
+                av *= p;
+                pv *= beta;
+                pa *= p;
+                collect(s, k);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < KS; k++)
+                if (k < nv) {   // uniform
+                    const int t = t0 + k, c = tc[TRS > 0 ? k / (TRS > 0 ? TRS : 1) : 0];
+                    // a spike of the block before counts at this block's first step
+                    if (TRS > 0 && k % (TRS > 0 ? TRS : 1) == 0 && k > 0) {
+                        const int cp = tc[k / (TRS > 0 ? TRS : 1) - 1];
+                        tl = cp < ST_FAR ? cp : tl;
+                    }
+                    tl = t - 1 == c ? c : tl;
+                    const bool spv = t - 1 == tl, gate = t - tl >= TR;
+                    const double x = gate ? (double)s.x[k] + bias : 0.0;
+                    const double Wn = fma(beta, W, V - x), Vn = fma(beta, V, omb * x);
+                    const double Un = fma(beta, U, gate ? omb : 0.0);
+                    W = spv ? 0.0 : Wn;
+                    V = spv ? 0.0 : Vn;
+                    U = spv ? 0.0 : Un;
+                    pv = spv ? 0.0 : pv * beta;
+                    Q = fma(p, Q, av);
+                    av = fma(p, av, spv ? 1.0 : 0.0);
+                    pa *= p;
+                    collect(s, k);
+                }
+        }
+        const int cl = tc[M - 1];
+        if constexpr (M > 1) {   // (blocks past the chunk's end repeat its last one)
+#pragma unroll
+            for (int m = 0; m < M; m++) tl = tc[m] < t0 + KS ? tc[m] : tl;
+        } else {
+            tl = cl < t0 + KS ? cl : tl;
+        }
+    };
+
+    Slot ring[RING];
+    Pos ql{blk0, 0}, qc{blk0, 0};
+#pragma unroll
+    for (int i = 0; i < RING - 1; i++) {
+        load(ring[i], ql);
+        ql = next(ql);
+    }
+    int r = 0;
+    for (; r + RING <= groups; r += RING) {
+#pragma unroll
+        for (int i = 0; i < RING; i++) {
+            load(ring[(i + RING - 1) % RING], ql);
+            ql = next(ql);
+            group(ring[i], qc);
+            qc = next(qc);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RING; i++)
+        if (r + i < groups) {   // uniform; at most RING - 1 groups, all loaded
+            group(ring[i], qc);
+            qc = next(qc);
+        }
+
+    if (n < N) {
+        const size_t BN = (size_t)a.B * N, S = a.chunks * BN;
+        double *o = a.part + (a.chunks > 1 ? 5 * BN : 0) + (size_t)ch * BN + (size_t)b * N + n;
+        o[0] = sb;
+        o[S] = dd * sp;
+        o[2 * S] = sd;
+        o[3 * S] = sth;
+        o[4 * S] = sbias;
+        if (a.chunks > 1) {
+            o[5 * S] = CB;
+            o[6 * S] = dd * CA;
+            o[7 * S] = pv;
+            o[8 * S] = pa;
+            o[9 * S] = W;
+            o[10 * S] = U;
+            o[11 * S] = Q;
+        }
+    }
+}
+
+// The chunks' sums of one (b, n) joined in time order: the W, U and Q that reach chunk c
+// are those of the chunks before it, decayed by its pv and pa. A thread each, so the
+// whole card reads the 96 bytes a chunk; k_finalize then sums over the batch.
+__global__ __launch_bounds__(64) void k_join_chunks(size_t BN, int chunks, const double *__restrict__ in,
+                                                    double *__restrict__ out) {
+    const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x, S = (size_t)chunks * BN;
+    if (i >= BN) return;
+    double s[5] = {0, 0, 0, 0, 0}, W = 0.0, U = 0.0, Q = 0.0;
+#pragma unroll 2
+    for (int c = 0; c < chunks; c++) {
+        const double *q = in + (size_t)c * BN + i;
+        const double CB = q[5 * S], CA = q[6 * S], pv = q[7 * S], pa = q[8 * S];
+        s[0] += fma(CB, W, q[0]);
+        s[1] += fma(CA, Q, q[S]);
+        s[2] += q[2 * S];
+        s[3] += q[3 * S];
+        s[4] += fma(CB, U, q[4 * S]);
+        W = fma(pv, W, q[9 * S]);
+        U = fma(pv, U, q[10 * S]);
+        Q = fma(pa, Q, q[11 * S]);
+    }
+#pragma unroll
+    for (int q = 0; q < 5; q++) out[q * BN + i] = s[q];
+}
+
+template <int KS, int TRS>
+void stream_launch(const BwdArgs &a, unsigned grid, hipStream_t st) {
+    const dim3 blk(64 * ST_WAVES);
+    const bool gvt = a.gV || a.gTH;
+#define ALIF_ST(SG)                                                                                          \
+    do {                                                                                                     \
+        if (gvt) hipLaunchKernelGGL((k_bwd_stream<KS, TRS, true, SG>), dim3(grid), blk, 0, st, a);           \
+        else hipLaunchKernelGGL((k_bwd_stream<KS, TRS, false, SG>), dim3(grid), blk, 0, st, a);              \
+    } while (0)
+    if (a.surrogate == 1) ALIF_ST(1);
+    else if (a.surrogate == 2) ALIF_ST(2);
+    else ALIF_ST(0);
+#undef ALIF_ST
+}
+
+}  // namespace
+
+size_t bwd_stream_bytes(int B, int N, int chunks) {
+    return (size_t)(chunks > 1 ? 5 + 12 * (size_t)chunks : 5) * B * N * sizeof(double);
+}
+
+int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
+    const long long waves = (long long)B * ((N + 63) / 64);
+    if (waves == 0 || T == 0) return 1;
+    const int NB = (T + TR - 1) / TR;
+    long long c = (ST_TARGET_WAVES + waves - 1) / waves;
+    c = c < T / ST_MIN_STEPS ? c : T / ST_MIN_STEPS;
+    c = c < NB ? c : NB;
+    if (c <= 1) return 1;
+    const int nbc = (int)((NB + c - 1) / c), chunks = (NB + nbc - 1) / nbc;   // every chunk holds a block
+    return bwd_stream_bytes(B, N, chunks) <= max_bytes ? chunks : 1;
+}
+
+hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {
+    a.nbc = (a.NB + a.chunks - 1) / a.chunks;
+    a.n_groups = (a.N + 63) / 64;
+    const long long items = (long long)a.B * a.chunks * a.n_groups;
+    if (items == 0) return hipSuccess;
+    const unsigned grid = (unsigned)((items + ST_WAVES - 1) / ST_WAVES);
+    if (a.TR == 2) stream_launch<8, 2>(a, grid, st);
+    else if (a.TR == 3) stream_launch<6, 3>(a, grid, st);
+    else if (a.TR == 4) stream_launch<8, 4>(a, grid, st);
+    else {   // the fewest steps lost to the last group, then the longer group
+        int ks = 8, lost = (a.TR + 7) / 8 * 8 - a.TR;
+        for (int k = 7; k >= 5; k--) {
+            const int l = (a.TR + k - 1) / k * k - a.TR;
+            if (l < lost) { ks = k; lost = l; }
+        }
+        if (ks == 8) stream_launch<8, 0>(a, grid, st);
+        else if (ks == 7) stream_launch<7, 0>(a, grid, st);
+        else if (ks == 6) stream_launch<6, 0>(a, grid, st);
+        else stream_launch<5, 0>(a, grid, st);
+    }
+    if (a.chunks > 1) {
+        const size_t BN = (size_t)a.B * a.N;
+        hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)((BN + 63) / 64)), dim3(64), 0, st, BN, a.chunks,
+                           (const double *)(a.part + 5 * BN), a.part);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace alif
