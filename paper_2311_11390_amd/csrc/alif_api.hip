@@ -281,7 +281,7 @@ int alif_input_current(const alif_desc *desc, const void *input, const float *W,
     in.kind = desc->input_kind;
     in.ptr = input;
     hipError_t e = gemm_input_current((size_t)p.B * p.T, p.N, p.n_in, in, W, bias, current,
-                                      desc->gemm_precision == ALIF_GEMM_BF16, (hipStream_t)stream);
+                                      desc->gemm_precision == ALIF_GEMM_BF16, false, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "input-current GEMM");
     return ALIF_OK;
 }
@@ -361,7 +361,7 @@ int alif_forward(const alif_desc *desc, const alif_params *prm, const void *inpu
         const size_t sbytes = (size_t)p.B * p.T * p.N *
                               (desc->spike_dtype == ALIF_SPIKES_U8 ? 1 : (desc->spike_dtype == ALIF_SPIKES_BF16 ? 2 : 4));
         hipError_t e = gemm_input_current((size_t)p.B * p.T, p.N, p.n_in, in, W, prm->bias, current,
-                                          desc->gemm_precision == ALIF_GEMM_BF16, st, spikes, sbytes);
+                                          desc->gemm_precision == ALIF_GEMM_BF16, true, st, spikes, sbytes);
         if (e != hipSuccess) return hip_fail(e, "input-current GEMM");
         I = current;
         bias_k = nullptr;
@@ -670,7 +670,7 @@ int alif_forward_recurrent(const alif_desc *desc, const alif_params *prm, const 
         in.kind = desc->input_kind;
         in.ptr = input;
         // the spike output, written only at the end, holds the bfloat16 weights meanwhile
-        e = gemm_input_current((size_t)p.B * p.T, p.N, p.n_in, in, W, prm->bias, current, bf16, st, spikes,
+        e = gemm_input_current((size_t)p.B * p.T, p.N, p.n_in, in, W, prm->bias, current, bf16, true, st, spikes,
                                BTN * (size_t)spike_elem_bytes(desc->spike_dtype));
         if (e != hipSuccess) return hip_fail(e, "input-current GEMM");
         bias_k = nullptr;

@@ -16,8 +16,9 @@ struct GemmIn {
 // gemm_wbf16_bytes(N, K) bytes (16-byte aligned; nullptr: none) receives W rounded
 // to bfloat16 once, so that the GEMM streams half the weight bytes and converts
 // only x.
+// fp32_order as in GemmArgs.
 hipError_t gemm_input_current(size_t M, int N, int K, GemmIn x, const float *W, const float *bias,
-                              float *out, bool bf16, hipStream_t st, void *scratch = nullptr,
+                              float *out, bool bf16, bool fp32_order, hipStream_t st, void *scratch = nullptr,
                               size_t scratch_bytes = 0);
 // bytes of the bfloat16 copy of a [N][K] weight matrix, as is or transposed, with
 // rows padded to 16 bytes
@@ -73,10 +74,18 @@ struct GemmArgs {
     // that picks between this GEMM and another way of computing C on the device).
     const unsigned long long *skip_cnt;
     unsigned long long skip_le;
+    // FP32: sum by v_mfma_f32_16x16x4_f32 over increasing k (the currents a layer's
+    // spikes come from, whose bits decide near-threshold crossings)
+    bool fp32_order;
 };
 __device__ __forceinline__ bool gemm_gated_off(const unsigned long long *cnt, unsigned long long le) {
     return cnt != nullptr && *cnt <= le;
 }
 hipError_t gemm_launch(const GemmArgs &g, bool bf16, hipStream_t st);
+
+// FP32 GEMM on the bfloat16 matrix cores (alif_gemm_split.hip): whether it takes the
+// call's layouts and alignment; its launch (*splits: K splits written to g.C_part).
+bool gemm_split_ok(const GemmArgs &g);
+hipError_t gemm_split_launch(const GemmArgs &g, hipStream_t st, int *splits);
 
 }  // namespace alif

@@ -590,9 +590,10 @@ __global__ void k_split_reduce(long long MN, int N, int splits, const float *P, 
 hipError_t gemm_launch(const GemmArgs &g, bool bf16, hipStream_t st) {
     if (g.M == 0 || g.N == 0) return hipSuccess;
     if (bf16 && gemm_big_ok(g)) return gemm_big_launch(g, st);
-    if (tiled_ok(g, bf16)) {
+    const bool split = !bf16 && !g.fp32_order && gemm_split_ok(g);
+    if (split || tiled_ok(g, bf16)) {
         int splits = 1;
-        hipError_t e = bf16 ? tiled_launch<true>(g, st, &splits) : tiled_launch<false>(g, st, &splits);
+        hipError_t e = split ? gemm_split_launch(g, st, &splits) : bf16 ? tiled_launch<true>(g, st, &splits) : tiled_launch<false>(g, st, &splits);
         if (e != hipSuccess || splits == 1) return e;
         const long long MN = g.M * (long long)g.N;
         hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, MN, g.N,
@@ -664,8 +665,10 @@ constexpr double EV_MIN = 16777216.0;
 static int ev_cut(bool bf16, int N) { return bf16 ? (N >= 256 ? 64 : 256) : 16; }
 
 hipError_t gemm_input_current(size_t M, int N, int K, GemmIn x, const float *W, const float *bias,
-                              float *out, bool bf16, hipStream_t st, void *scratch, size_t scratch_bytes) {
+                              float *out, bool bf16, bool fp32_order, hipStream_t st, void *scratch,
+                              size_t scratch_bytes) {
     GemmArgs g{};
+    g.fp32_order = fp32_order;
     g.M = (long long)M; g.N = N; g.K = K;
     g.A = x.ptr; g.a_dt = dt_of(x.kind); g.lda = K; g.a_kc = 1;
     g.B = W; g.b_dt = 0; g.ldb = K; g.b_kc = 1;
