@@ -44,6 +44,7 @@ constexpr int ST_FAR = 1 << 30;
 // 4 x 2048 x 20000 at T_R 20 (354 / 278 / 282 / 310).
 constexpr int ST_TARGET_WAVES = 3072;
 constexpr int ST_MIN_STEPS = 64;   // a chunk's set-up (five exponentials, a first load) is worth about 16 steps
+constexpr int ST_MAX_CHUNKS = 64;  // the join walks an eighth of them in sequence, 1.4 us each
 constexpr int ST_RING = 2;         // groups of steps in registers; 3 measured the same
 
 // KS: steps loaded and processed together; TRS: T_R where a group of KS steps holds
@@ -245,29 +246,60 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     }
 }
 
-// The chunks' sums of one (b, n) joined in time order: the W, U and Q that reach chunk c
-// are those of the chunks before it, decayed by its pv and pa. A thread each, so the
-// whole card reads the 96 bytes a chunk; k_finalize then sums over the batch.
-__global__ __launch_bounds__(64) void k_join_chunks(size_t BN, int chunks, const double *__restrict__ in,
-                                                    double *__restrict__ out) {
-    const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x, S = (size_t)chunks * BN;
-    if (i >= BN) return;
-    double s[5] = {0, 0, 0, 0, 0}, W = 0.0, U = 0.0, Q = 0.0;
-#pragma unroll 2
-    for (int c = 0; c < chunks; c++) {
-        const double *q = in + (size_t)c * BN + i;
-        const double CB = q[5 * S], CA = q[6 * S], pv = q[7 * S], pa = q[8 * S];
-        s[0] += fma(CB, W, q[0]);
-        s[1] += fma(CA, Q, q[S]);
-        s[2] += q[2 * S];
-        s[3] += q[3 * S];
-        s[4] += fma(CB, U, q[4 * S]);
-        W = fma(pv, W, q[9 * S]);
-        U = fma(pv, U, q[10 * S]);
-        Q = fma(pa, Q, q[11 * S]);
+// The chunks' sums of one (b, n) joined in time order: the W, U and Q that reach a chunk
+// are those of the chunks before it, decayed by its pv and pa. Two neighbouring chunks
+// make one of the same form (Part::then), so JG threads compose a share of the chunks each
+// and one adds the shares up through LDS: 250 chunks of a single row take 31 loads in
+// sequence instead of 250. k_finalize then sums over the batch.
+constexpr int JG = 8;
+
+struct Part {
+    double b, p, d, th, bias, CB, CA, pv, pa, W, U, Q;
+    // this chunk followed by x
+    __device__ __forceinline__ void then(const Part &x) {
+        b += fma(x.CB, W, x.b);
+        p += fma(x.CA, Q, x.p);
+        d += x.d;
+        th += x.th;
+        bias += fma(x.CB, U, x.bias);
+        CB = fma(x.CB, pv, CB);
+        CA = fma(x.CA, pa, CA);
+        W = fma(x.pv, W, x.W);
+        U = fma(x.pv, U, x.U);
+        Q = fma(x.pa, Q, x.Q);
+        pv *= x.pv;
+        pa *= x.pa;
     }
-#pragma unroll
-    for (int q = 0; q < 5; q++) out[q * BN + i] = s[q];
+};
+
+__global__ __launch_bounds__(64 * JG) void k_join_chunks(size_t BN, int chunks, const double *__restrict__ in,
+                                                         double *__restrict__ out) {
+    __shared__ double sh[JG][12][64];
+    const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const size_t i = (size_t)blockIdx.x * 64 + l, S = (size_t)chunks * BN;
+    const int per = (chunks + JG - 1) / JG, c1 = min(chunks, (g + 1) * per);
+    Part t{0, 0, 0, 0, 0, 0, 0, 1, 1, 0, 0, 0};   // no step
+    if (i < BN)
+#pragma unroll 2
+        for (int c = g * per; c < c1; c++) {
+            const double *q = in + (size_t)c * BN + i;
+            t.then(Part{q[0], q[S], q[2 * S], q[3 * S], q[4 * S], q[5 * S], q[6 * S], q[7 * S], q[8 * S], q[9 * S],
+                        q[10 * S], q[11 * S]});
+        }
+    double *o = &sh[g][0][l];
+    o[0] = t.b; o[64] = t.p; o[128] = t.d; o[192] = t.th; o[256] = t.bias; o[320] = t.CB;
+    o[384] = t.CA; o[448] = t.pv; o[512] = t.pa; o[576] = t.W; o[640] = t.U; o[704] = t.Q;
+    __syncthreads();
+    if (g != 0 || i >= BN) return;
+    for (int h = 1; h < JG; h++) {
+        const double *q = &sh[h][0][l];
+        t.then(Part{q[0], q[64], q[128], q[192], q[256], q[320], q[384], q[448], q[512], q[576], q[640], q[704]});
+    }
+    out[i] = t.b;
+    out[BN + i] = t.p;
+    out[2 * BN + i] = t.d;
+    out[3 * BN + i] = t.th;
+    out[4 * BN + i] = t.bias;
 }
 
 template <int KS, int TRS>
@@ -298,6 +330,7 @@ int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
     long long c = (ST_TARGET_WAVES + waves - 1) / waves;
     c = c < T / ST_MIN_STEPS ? c : T / ST_MIN_STEPS;
     c = c < NB ? c : NB;
+    c = c < ST_MAX_CHUNKS ? c : ST_MAX_CHUNKS;
     if (c <= 1) return 1;
     const int nbc = (int)((NB + c - 1) / c), chunks = (NB + nbc - 1) / nbc;   // every chunk holds a block
     return bwd_stream_bytes(B, N, chunks) <= max_bytes ? chunks : 1;
@@ -325,7 +358,7 @@ hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {
     }
     if (a.chunks > 1) {
         const size_t BN = (size_t)a.B * a.N;
-        hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)((BN + 63) / 64)), dim3(64), 0, st, BN, a.chunks,
+        hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)((BN + 63) / 64)), dim3(64 * JG), 0, st, BN, a.chunks,
                            (const double *)(a.part + 5 * BN), a.part);
     }
     return hipGetLastError();
