@@ -617,6 +617,9 @@ RecLayout rec_layout(const alif_desc *d, const Prob &p) {
     L.blk = align256((size_t)p.B * p.TR * p.N * sb);
     L.spikes = L.blk * p.NB;
     L.state = align256((size_t)p.B * p.N * 8) * 4 + align256((size_t)p.B * p.N * 4) * 2;
+    // (the workgroup-per-element path keeps its spike steps and state in the first two regions)
+    const size_t fused = recurrent_fused_bytes(p.B, p.NB, p.N, p.TR);
+    if (L.spikes + L.state < fused) L.state = fused - L.spikes;
     L.wt = align256((size_t)p.N * p.N * 4);
     const size_t fwd = L.spikes + L.state + L.wt;
     // weight gradient: the event path's count, masks and partials; the dense path's
@@ -687,9 +690,7 @@ int alif_forward_recurrent(const alif_desc *desc, const alif_params *prm, const 
     double *sa[2] = {(double *)(stb + 2 * s8), (double *)(stb + 3 * s8)};
     int32_t *sts[2] = {(int32_t *)(stb + 4 * s8), (int32_t *)(stb + 4 * s8 + s4)};
     float *wrt = (float *)(stb + L.state);
-    e = launch_transpose(p.N, W_rec, wrt, st);
-    if (e != hipSuccess) return hip_fail(e, "W_rec transpose launch");
-    if (fused) {   // the whole block loop in one launch
+    if (fused) {   // a workgroup per batch element
         RecArgs r{};
         r.B = p.B; r.T = p.T; r.N = p.N; r.TR = p.TR; r.NB = p.NB; r.D = D;
         r.ring = recurrent_ring_slots(p.TR, D);
@@ -698,6 +699,7 @@ int alif_forward_recurrent(const alif_desc *desc, const alif_params *prm, const 
         r.I = current;
         r.bias_k = bias_k;
         r.tau_m = prm->tau_mem_ms; r.tau_a = prm->tau_adapt_ms; r.d = prm->d; r.theta0 = prm->theta0;
+        r.Wrec = W_rec;
         r.WrecT = wrt;
         r.spikes = spikes;
         r.spike_dtype = desc->spike_dtype;
@@ -705,10 +707,13 @@ int alif_forward_recurrent(const alif_desc *desc, const alif_params *prm, const 
         r.TH = theta;
         if (carries) r.ck = carry_view(carries, p);
         r.status = status;
+        recurrent_fused_ws(r, ws);   // (over the per-block path's staging, in front of W_rec transposed)
         e = launch_recurrent_fused(r, st);
         if (e != hipSuccess) return hip_fail(e, "recurrent layer launch");
         return ALIF_OK;
     }
+    e = launch_transpose(p.N, W_rec, wrt, st);
+    if (e != hipSuccess) return hip_fail(e, "W_rec transpose launch");
     const int nwg = block_neurons_per_wg(block_config(p.TR).seg);
     const size_t TN = (size_t)p.T * p.N, TRN = (size_t)p.TR * p.N;
     const int sb = spike_elem_bytes(desc->spike_dtype);

@@ -105,16 +105,16 @@ hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// one-launch recurrent layer (alif_recurrent_impl.h)
+// recurrent layer of one workgroup per batch element (alif_recurrent_impl.h)
 // ---------------------------------------------------------------------------
 template <int S, int L, int NG>
-hipError_t recurrent_fused_launch(const RecArgs &, hipStream_t);
+hipError_t recurrent_fused_launch(RecArgs, hipStream_t);
 #define ALIF_REC_G2(X) X(1, 2) X(1, 3) X(1, 4) X(2, 3) X(2, 4) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(4, 8) X(8, 5) \
     X(8, 6) X(8, 8) X(8, 10) X(8, 12) X(8, 13) X(8, 14) X(8, 15) X(8, 16)
 #define ALIF_REC_G4(X) X(1, 2) X(1, 3) X(1, 4) X(2, 3) X(2, 4) X(4, 3) X(4, 4) X(4, 5) X(4, 6) X(4, 8) X(4, 9) \
     X(4, 10) X(4, 11) X(4, 12) X(4, 13) X(4, 14) X(4, 15) X(4, 16)
-#define ALIF_REC_EXT2(S, L) extern template hipError_t recurrent_fused_launch<S, L, 2>(const RecArgs &, hipStream_t);
-#define ALIF_REC_EXT4(S, L) extern template hipError_t recurrent_fused_launch<S, L, 4>(const RecArgs &, hipStream_t);
+#define ALIF_REC_EXT2(S, L) extern template hipError_t recurrent_fused_launch<S, L, 2>(RecArgs, hipStream_t);
+#define ALIF_REC_EXT4(S, L) extern template hipError_t recurrent_fused_launch<S, L, 4>(RecArgs, hipStream_t);
 ALIF_REC_G2(ALIF_REC_EXT2)
 ALIF_REC_G4(ALIF_REC_EXT4)
 
@@ -143,6 +143,28 @@ static size_t rec_smem_bytes(const RecConfig &c, int TR, int D) {
 bool recurrent_fused_ok(int N, int TR, int D) {
     const RecConfig c = rec_config(N, TR);
     return c.ng != 0 && D >= TR && rec_smem_bytes(c, TR, D) <= (size_t)160 * 1024;
+}
+
+static size_t rec_a256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// (at most 8 segments a block)
+size_t recurrent_fused_bytes(int B, int NB, int N, int TR) {
+    const size_t bn = (size_t)B * N;
+    return rec_a256(bn * NB) + rec_a256((size_t)B * NB * 8 * 4) + 2 * rec_a256(bn * 8) + rec_a256(bn * 4) +
+           rec_a256((size_t)N * TR * 8);
+}
+
+void recurrent_fused_ws(RecArgs &a, void *ws) {
+    const size_t bn = (size_t)a.B * a.N;
+    char *p = static_cast<char *>(ws);
+    a.ts = reinterpret_cast<uint8_t *>(p);
+    p += rec_a256(bn * a.NB);
+    a.hits = reinterpret_cast<uint32_t *>(p);
+    p += rec_a256((size_t)a.B * a.NB * 8 * 4);
+    a.st_v = reinterpret_cast<double *>(p);
+    a.st_a = reinterpret_cast<double *>(p + rec_a256(bn * 8));
+    a.st_ts = reinterpret_cast<int32_t *>(p + 2 * rec_a256(bn * 8));
+    a.pd = reinterpret_cast<double *>(p + 2 * rec_a256(bn * 8) + rec_a256(bn * 4));
 }
 
 hipError_t launch_recurrent_fused(const RecArgs &a, hipStream_t st) {

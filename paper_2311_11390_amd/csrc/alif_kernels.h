@@ -65,7 +65,7 @@ struct BwdArgs {
     int chunks, nbc;  // streaming backward: time chunks a row, blocks a chunk (nbc set by its launch)
 };
 
-// Recurrent layer in one launch (one workgroup per batch element)
+// Recurrent layer of one workgroup per batch element
 struct RecArgs {
     int B, T, N, TR, NB;
     int D;                // recurrent delay in steps, >= T_R
@@ -75,12 +75,23 @@ struct RecArgs {
     float *I;             // [B][T][N] the whole current (every row written)
     const float *bias_k;  // added in-kernel, nullable
     const float *tau_m, *tau_a, *d, *theta0;
-    const float *WrecT;   // [N][N], WrecT[j][i] = W_rec[i][j]
+    const float *Wrec;    // [N][N]
+    float *WrecT;         // [N][N] scratch: WrecT[j][i] = W_rec[i][j], written by the launch
     void *spikes;         // [B][T][N]
     int spike_dtype;
     float *V, *TH;
     CarryView ck;
     unsigned *status;
+    // without traces: the spike step of every block and neuron (0 none) and the state that
+    // crosses launches, in the caller's workspace (recurrent_fused_bytes)
+    uint8_t *ts;          // [B][NB][N]
+    uint32_t *hits;       // [B][NB][segments]: the steps of each segment that recurrent input reaches
+    double *st_v, *st_a;  // [B][N]
+    int32_t *st_ts;       // [B][N]
+    double *pd;           // [N][T_R] powers of p
+    // set by the launch: the chain's blocks, the blocks to expand, the chain's workgroups,
+    // whether rows take four neurons a lane
+    int nb0, nb1, xb0, xb1, core, vec4;
 };
 
 struct SeqArgs {
@@ -140,6 +151,9 @@ hipError_t launch_recurrent_events(int B, int TR, int rows, int N, long long bst
 bool recurrent_fused_ok(int N, int TR, int D);
 int recurrent_ring_slots(int TR, int D);
 hipError_t launch_recurrent_fused(const RecArgs &a, hipStream_t st);
+// its workspace (ts, hits, st_v, st_a, st_ts, pd, each 256-byte aligned, in that order)
+size_t recurrent_fused_bytes(int B, int NB, int N, int TR);
+void recurrent_fused_ws(RecArgs &a, void *ws);
 // The weight gradient of a spike-driven projection from the spike events
 // (dW[i][j] = sum over b and u < T - D of S[b][u][j] gI[b][u + D][i], Nj spike
 // columns j, Ni gradient columns i; D = 0 for a feed-forward projection) into the
