@@ -24,9 +24,9 @@ def test_slices_equal_one_launch(TR, delay, T, N, sdt, spikes_in):
     P = to_dev(random_params(TR, N, tm=(2.0, 30.0), d=(0.0, 0.5)))
     if spikes_in:
         x = (torch.rand(B, T, n_in, generator=g, device="cuda") < 0.3).to(torch.uint8)
-        W = torch.randn(N, n_in, generator=g, device="cuda")
+        W = torch.randn(N, n_in, generator=g, device="cuda") + 0.4
     else:
-        x = torch.randn(B, T, N, generator=g, device="cuda") * 3.0
+        x = torch.randn(B, T, N, generator=g, device="cuda") * 3.0 + 1.5  # (noise alone averages out at fine steps)
         W = None
     Wrec = torch.randn(N, N, generator=g, device="cuda") * 0.3
     a = alif.forward_recurrent(x, P, dt, 2.0, Wrec, W, spike_dtype=sdt, delay=delay)
