@@ -1,6 +1,6 @@
-// Parameter-gradient backward without an input-current gradient (the fits: the
-// gradients of tau_mem, tau_adapt, d, theta0 and bias alone), as one pass forward
-// in time over independent time chunks.
+// Backward as passes over independent time chunks: the gradients of tau_mem, tau_adapt,
+// d, theta0 and bias (all a fit asks for) in one pass forward in time, and dL/dI where it
+// is wanted (bwd_stream_gi says by which calls) in one more backward in time.
 //
 // The sums the reverse adjoint collects,
 //   dbeta = sum_t src[t] W[t],   dbias = sum_t src[t] U[t],
@@ -50,7 +50,8 @@ constexpr int ST_RING = 2;         // groups of steps in registers; 3 measured t
 // KS: steps loaded and processed together; TRS: T_R where a group of KS steps holds
 // whole blocks of TRS steps, 0: a block of T_R >= KS steps in ceil(T_R / KS) groups,
 // the last one partial.
-template <int KS, int TRS, bool GVT, int SG>
+// GI: each step's src goes into the input-current gradient, for k_gi_reverse.
+template <int KS, int TRS, bool GVT, bool GI, int SG>
 __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     constexpr int M = TRS > 0 ? KS / TRS : 1;   // blocks a group
     constexpr int RING = ST_RING;               // groups in registers
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
 
     const size_t TN = (size_t)a.T * N, CN = (size_t)(a.NB + 1) * N;
     // an absent gradient reads the input's rows instead and is zeroed at its use (without
-    // dL/dV and dL/dtheta, an absent dL/dS leaves nothing to sum)
+    // dL/dV, dL/dtheta and dL/dI, an absent dL/dS leaves nothing to do)
     const float *I = a.I + b * TN;
     const bool hasS = a.gS != nullptr, hasV = GVT && a.gV != nullptr, hasT = GVT && a.gTH != nullptr;
     const float *gS = hasS ? a.gS + b * TN : I, *gV = hasV ? a.gV + b * TN : I, *gT = hasT ? a.gTH + b * TN : I;
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     };
     // group q of the chunk: blocks [blk, blk + M), steps from t (all uniform)
     const int gpb = TRS > 0 ? 1 : (TR + KS - 1) / KS;
-    const int groups = !GVT && !hasS ? 0 : TRS > 0 ? (blk1 - blk0 + M - 1) / M : (blk1 - blk0) * gpb;
+    const int groups = !GVT && !GI && !hasS ? 0 : TRS > 0 ? (blk1 - blk0 + M - 1) / M : (blk1 - blk0) * gpb;
     struct Pos {
         int blk, j;
     };
@@ -107,6 +108,8 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     const rsrc_t rI = make_rsrc(I, (uint32_t)(TN * 4)), rS = make_rsrc(gS, (uint32_t)(TN * 4));
     const rsrc_t rV = make_rsrc(gV, (uint32_t)(TN * 4)), rT = make_rsrc(gT, (uint32_t)(TN * 4));
     const rsrc_t rC = make_rsrc(cts, (uint32_t)CN);
+    const rsrc_t rG = make_rsrc(GI ? a.gI + b * TN : nullptr, GI ? (uint32_t)(TN * 4) : 0u);
+    const uint32_t g4 = n < N ? n4 : ALIF_OOB;   // (a store out of range is dropped)
     auto ldf = [&](rsrc_t r, uint32_t row) __attribute__((always_inline)) {
         return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, n4, row, 0));
     };
@@ -126,10 +129,10 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
         for (int m = 0; m < M; m++) s.ts[m] = __builtin_amdgcn_raw_buffer_load_b8(rC, nc, (min(q.blk + m, blk1 - 1) + 1) * N, 0);
     };
 
-    // the local terms of a step, once V, a and the sensitivities are its own
-    auto collect = [&](const Slot &s, int k) __attribute__((always_inline)) {
+    // the local terms of step t0 + k, once V, a and the sensitivities are its own
+    auto collect = [&](const Slot &s, int k, int t0) __attribute__((always_inline)) {
         const double u = V - fma(dd, av, th0);
-        const float gs = !GVT || hasS ? s.gs[k] : 0.0f;
+        const float gs = (!GVT && !GI) || hasS ? s.gs[k] : 0.0f;
         const double q = (double)(gs * surrogate_grad<SG>((float)u, a.slope));
         double src = q, lt = -q;
         if constexpr (GVT) {
@@ -143,6 +146,8 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
         sth += lt;
         CB = fma(src, pv, CB);
         CA = fma(lt, pa, CA);
+        if constexpr (GI)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)src), rG, g4, (uint32_t)((t0 + k) * N) * 4u, 0);
     };
     auto group = [&](Slot &s, Pos q) __attribute__((always_inline)) {
         const int t0 = step0(q);
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
                 av *= p;
                 pv *= beta;
                 pa *= p;
-                collect(s, k);
+                collect(s, k, t0);
             }
         } else {
 #pragma unroll
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
                     Q = fma(p, Q, av);
                     av = fma(p, av, spv ? 1.0 : 0.0);
                     pa *= p;
-                    collect(s, k);
+                    collect(s, k, t0);
                 }
         }
         const int cl = tc[M - 1];
@@ -302,19 +307,140 @@ __global__ __launch_bounds__(64 * JG) void k_join_chunks(size_t BN, int chunks, 
     out[4 * BN + i] = t.bias;
 }
 
+// The input-current gradient from the src a forward pass left in its place: the adjoint
+// of the membrane, backward in time over the same chunks,
+//   lam[t] = src[t] + nu[t+1],  nu[t] = beta (1 - S[t-1]) lam[t],  gI[t] = (1 - beta) gate[t] lam[t],
+// with the nu that reaches a chunk composed from the CB and pv of the chunks behind it.
+// Six vector instructions a step, in FP64 but for src (the FP32 value the block backward
+// sums) and gI. What bounds it: HBM, a read and a write a step.
+template <int KS, int TRS>
+__global__ __launch_bounds__(64 * ST_WAVES) void k_gi_reverse(BwdArgs a) {
+    constexpr int M = TRS > 0 ? KS / TRS : 1;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int item = xcd_remap(blockIdx.x, gridDim.x) * ST_WAVES + wave;
+    const int bc = item / a.n_groups, g = item - bc * a.n_groups;
+    const int b = bc / a.chunks, ch = bc - b * a.chunks;
+    if (b >= a.B) return;   // no barrier in this kernel
+    const int N = a.N, TR = TRS > 0 ? TRS : a.TR;
+    const int n = g * 64 + lane, nc = min(n, N - 1);
+    const int blk0 = ch * a.nbc, blk1 = min(a.NB, blk0 + a.nbc);
+    const int tbeg = blk0 * TR, tend = min(a.T, blk1 * TR);
+
+    const double dt = a.dt, tm = a.tau_m[nc];
+    const double beta = exp(-dt / tm), omb = -expm1(-dt / tm);
+    const size_t BN = (size_t)a.B * N, S = a.chunks * BN, TN = (size_t)a.T * N, CN = (size_t)(a.NB + 1) * N;
+    double nu = 0.0;
+    {
+        const double *q = a.part + 5 * BN + (size_t)b * N + nc;
+#pragma unroll 4
+        for (int c = a.chunks - 1; c > ch; c--) nu = fma(q[7 * S + c * BN], nu, q[5 * S + c * BN]);
+    }
+
+    struct Slot {
+        float x[KS];
+        int ts[M + 1];   // spike steps of the block before the group's first, then the group's
+    };
+    const int gpb = TRS > 0 ? 1 : (TR + KS - 1) / KS;
+    const int groups = TRS > 0 ? (blk1 - blk0 + M - 1) / M : (blk1 - blk0) * gpb;
+    struct Pos {
+        int blk, j;
+    };
+    auto step0 = [&](Pos q) { return TRS > 0 ? q.blk * TR : q.blk * TR + q.j * KS; };
+    auto next = [&](Pos q) {   // (before the chunk's first block: loaded from that block, not used)
+        if constexpr (TRS > 0) return Pos{q.blk - M, 0};
+        else return q.j > 0 ? Pos{q.blk, q.j - 1} : Pos{q.blk - 1, gpb - 1};
+    };
+    const uint32_t n4 = (uint32_t)nc * 4u, g4 = n < N ? n4 : ALIF_OOB;
+    const rsrc_t rG = make_rsrc(a.gI + b * TN, (uint32_t)(TN * 4)), rC = make_rsrc(a.ck.ts + b * CN, (uint32_t)CN);
+    auto load = [&](Slot &s, Pos q) __attribute__((always_inline)) {
+        const int t = step0(q);
+#pragma unroll
+        for (int k = 0; k < KS; k++)
+            s.x[k] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                rG, n4, (uint32_t)(max(min(t + k, tend - 1), tbeg) * N) * 4u, 0));
+#pragma unroll
+        for (int m = 0; m <= M; m++)
+            s.ts[m] = __builtin_amdgcn_raw_buffer_load_b8(rC, nc, max(min(q.blk + m, blk1), blk0) * N, 0);
+    };
+    auto group = [&](const Slot &s, Pos q) __attribute__((always_inline)) {
+        const int t0 = step0(q);
+        int nv = min(KS, tend - t0);
+        if constexpr (TRS == 0) nv = min(nv, TR - q.j * KS);
+        int tc[M + 1];   // spike step, ST_FAR if none; the first: -ST_FAR if none
+#pragma unroll
+        for (int m = 0; m <= M; m++)
+            tc[m] = s.ts[m] > 0 ? (q.blk + m - 1) * TR + min(s.ts[m], TR) - 1 : (m ? ST_FAR : -ST_FAR);
+        bool act = t0 - tc[0] < TR;
+#pragma unroll
+        for (int m = 1; m <= M; m++) act |= tc[m] < t0 + KS - 1;
+        auto put = [&](int k, double v) __attribute__((always_inline)) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)v), rG, g4, (uint32_t)((t0 + k) * N) * 4u, 0);
+        };
+        if (nv == KS && !__any(act)) {   // no lane has a reset or a mask in this group
+#pragma unroll
+            for (int k = KS - 1; k >= 0; k--) {
+                const double lam = (double)s.x[k] + nu;
+                nu = beta * lam;
+                put(k, omb * lam);
+            }
+        } else {
+#pragma unroll
+            for (int k = KS - 1; k >= 0; k--)
+                if (k < nv) {   // uniform
+                    constexpr int W = TRS > 0 ? TRS : KS;
+                    const int t = t0 + k, c = tc[k / W + 1];
+                    int cp = tc[k / W];   // the block before's
+                    cp = cp == ST_FAR ? -ST_FAR : cp;
+                    const bool spv = t - 1 == c || t - 1 == cp, gate = t <= c && t - cp >= TR;
+                    const double lam = (double)s.x[k] + nu;
+                    nu = (spv ? 0.0 : beta) * lam;
+                    put(k, gate ? omb * lam : 0.0);
+                }
+        }
+    };
+
+    Slot ring[ST_RING];
+    Pos ql = TRS > 0 ? Pos{blk0 + (groups - 1) * M, 0} : Pos{blk1 - 1, gpb - 1}, qc = ql;
+#pragma unroll
+    for (int i = 0; i < ST_RING - 1; i++) {
+        load(ring[i], ql);
+        ql = next(ql);
+    }
+    int r = 0;
+    for (; r + ST_RING <= groups; r += ST_RING) {
+#pragma unroll
+        for (int i = 0; i < ST_RING; i++) {
+            load(ring[(i + ST_RING - 1) % ST_RING], ql);
+            ql = next(ql);
+            group(ring[i], qc);
+            qc = next(qc);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ST_RING; i++)
+        if (r + i < groups) {   // uniform; at most ST_RING - 1 groups, all loaded
+            group(ring[i], qc);
+            qc = next(qc);
+        }
+}
+
 template <int KS, int TRS>
 void stream_launch(const BwdArgs &a, unsigned grid, hipStream_t st) {
     const dim3 blk(64 * ST_WAVES);
-    const bool gvt = a.gV || a.gTH;
+    const bool gvt = a.gV || a.gTH, gi = a.gI != nullptr;
 #define ALIF_ST(SG)                                                                                          \
     do {                                                                                                     \
-        if (gvt) hipLaunchKernelGGL((k_bwd_stream<KS, TRS, true, SG>), dim3(grid), blk, 0, st, a);           \
-        else hipLaunchKernelGGL((k_bwd_stream<KS, TRS, false, SG>), dim3(grid), blk, 0, st, a);              \
+        if (gvt && gi) hipLaunchKernelGGL((k_bwd_stream<KS, TRS, true, true, SG>), dim3(grid), blk, 0, st, a); \
+        else if (gvt) hipLaunchKernelGGL((k_bwd_stream<KS, TRS, true, false, SG>), dim3(grid), blk, 0, st, a); \
+        else if (gi) hipLaunchKernelGGL((k_bwd_stream<KS, TRS, false, true, SG>), dim3(grid), blk, 0, st, a); \
+        else hipLaunchKernelGGL((k_bwd_stream<KS, TRS, false, false, SG>), dim3(grid), blk, 0, st, a);       \
     } while (0)
     if (a.surrogate == 1) ALIF_ST(1);
     else if (a.surrogate == 2) ALIF_ST(2);
     else ALIF_ST(0);
 #undef ALIF_ST
+    if (gi) hipLaunchKernelGGL((k_gi_reverse<KS, TRS>), dim3(grid), blk, 0, st, a);
 }
 
 }  // namespace
@@ -334,6 +460,26 @@ int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
     if (c <= 1) return 1;
     const int nbc = (int)((NB + c - 1) / c), chunks = (NB + nbc - 1) / nbc;   // every chunk holds a block
     return bwd_stream_bytes(B, N, chunks) <= max_bytes ? chunks : 1;
+}
+
+// Whether a backward that wants dL/dI streams. The block backward runs a row's blocks in
+// sequence, 64 to 256 neurons a workgroup, so a call that does not fill the card takes its
+// blocks times c(T_R) us; else it moves 12 bytes a step. Streaming cuts time as well, but moves
+// 20 bytes a step (the source written and read), after 35 us of launches, set-up and join.
+// Measured, us, block / streaming: T_R 2: 32 x 1000 x 512 209 / 80, 64 x 1000 x 512 221 / 149,
+// 64 x 1000 x 1024 247 / 293; T_R 10: 64 x 4000 x 256 339 / 294, 64 x 1000 x 512 125 / 153;
+// T_R 40: 16 x 20000 x 128 574 / 199, 32 x 1000 x 512 56 / 88. A segment of more than eight
+// steps that the block ends inside (and 16 with dL/dV or dL/dtheta) does not fit the block
+// kernel's registers, where streaming wins throughout: T_R 50: 129 / 67 (8 x 1000 x 1024),
+// 706 / 299 (64 x 1000 x 1024); T_R 100: 1334 / 551 (128 x 1000 x 1024).
+bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt, size_t max_bytes) {
+    const BlockConfig c = block_config(TR);
+    if (bwd_stream_chunks(B, T, N, TR, max_bytes) < bwd_stream_chunks(B, T, N, TR, SIZE_MAX)) return false;
+    if (c.seg == 8 && ((c.len >= 8 && TR != c.seg * c.len) || (gvt && c.len == 16))) return true;
+    const double steps = (double)B * T * N * 1e-6, NB = (T + TR - 1) / TR;
+    const double serial = 10.0 + NB * (c.seg == 1 ? 0.26 + 0.05 * TR : 0.6 + 0.02 * TR);
+    const double moved = 2.9 * steps * (gvt ? 20.0 / 12 : 1.0), stream = 35.0 + 4.2 * steps * (gvt ? 28.0 / 20 : 1.0);
+    return stream < (serial > moved ? serial : moved);
 }
 
 hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {

@@ -175,11 +175,13 @@ hipError_t launch_shift_time(int B, int T, int N, int D, int elem, const void *i
                              const unsigned long long *skip_cnt = nullptr, unsigned long long skip_le = 0);
 hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
-// The detached backward without an input-current gradient (alif_bwd_stream.hip): the
+// The detached backward as passes over time chunks (alif_bwd_stream.hip): the
 // time chunks a row is cut into (1 when their sums would pass max_bytes), the bytes of
 // `part` for that many, and the kernel (with the join of the chunks' sums).
 int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes);
 size_t bwd_stream_bytes(int B, int N, int chunks);
+// whether it takes a call with one (float gI)
+bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt, size_t max_bytes);
 hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st);
 hipError_t launch_decay_tables(int N, int TR, double dt, const float *tau_m, const float *tau_a,
                                float *beta_pow, float *p_pow, hipStream_t st);
