@@ -173,6 +173,9 @@ hipError_t launch_transpose(int N, const float *in, float *out, hipStream_t st);
 // skip_cnt set the kernel returns at entry when *skip_cnt <= skip_le as it starts
 hipError_t launch_shift_time(int B, int T, int N, int D, int elem, const void *in, void *out, hipStream_t st,
                              const unsigned long long *skip_cnt = nullptr, unsigned long long skip_le = 0);
+// blocks of one segment (T_R 2-4) without traces (alif_fwd_chain.hip): same bits; which calls
+bool fwd_chain_ok(int B, int N, int TR, bool traces, bool carries);
+hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st);
 hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 // The detached backward as passes over time chunks (alif_bwd_stream.hip): the
