@@ -57,27 +57,6 @@ __global__ void k_decay_tables(int N, int TR, double dt, const float *tau_m, con
 // ---------------------------------------------------------------------------
 // host-side dispatch
 // ---------------------------------------------------------------------------
-BlockConfig block_config(int TR) {
-    if (TR <= 2) return {1, 2};
-    if (TR == 3) return {1, 3};
-    if (TR == 4) return {1, 4};
-    if (TR <= 6) return {2, 3};
-    if (TR <= 8) return {2, 4};
-    if (TR <= 12) return {4, 3};
-    if (TR <= 16) return {4, 4};
-    if (TR <= 20) return {4, 5};
-    if (TR <= 24) return {4, 6};
-    if (TR <= 32) return {4, 8};
-    if (TR <= 40) return {8, 5};
-    if (TR <= 48) return {8, 6};
-    if (TR <= 64) return {8, 8};
-    if (TR <= 80) return {8, 10};
-    if (TR <= 96) return {8, 12};
-    if (TR <= 104) return {8, 13};
-    if (TR <= 112) return {8, 14};
-    if (TR <= 120) return {8, 15};
-    return {8, 16};
-}
 int block_neurons_per_wg(int seg) { return 64 * (seg >= 4 ? 1 : 4 / seg); }
 
 #define ALIF_CONFIGS(X) X(1, 2) X(1, 3) X(1, 4) X(2, 3) X(2, 4) X(4, 3) X(4, 4) X(4, 5) X(4, 6) \

@@ -1,34 +1,41 @@
-// Forward of blocks of two to four steps (a block is one segment of one lane), without
-// traces: the recurrence on one wave per 64 neurons, its loads and stores on others.
+// Forward without traces where the card is not full (T_R 2-32): the recurrence on one wave per
+// 64 neurons, its loads and stores on others.
 //
-// What bounds it: the chain. A row's T / T_R blocks follow each other, and one wave issues
-// an instruction about every five cycles, so a block costs what its wave issues. One wave
-// that does everything spends 95 of them a block at T_R 2, two thirds on addresses, loads,
-// spike and carry stores and a table read. Here
+// What bounds it: the chain. A row's T / T_R blocks follow each other, and one wave issues an
+// instruction about every five cycles, so a block costs what its wave issues. The block
+// kernel's one wave at T_R 2-4 issues 95 a block, two thirds of them addresses, loads, stores
+// and a table read; its two to four waves at T_R 5-32 meet at one or two barriers a block.
+// Here
 //   wave 1 loads the input FC_P groups of FC_G blocks ahead and leaves the drive
 //          (1 - beta)(I + b) in LDS,
-//   wave 0 runs the blocks of a group from LDS, state in registers (FP64 carries), and
-//          leaves each block's carry-in and spike step in LDS,
+//   wave 0 runs the blocks of a group from LDS, all segments of a block, state in registers
+//          (FP64 carries), and leaves each block's carry-in and spike step in LDS,
 //   wave 2 writes the spikes of the group before, wave 3 its carries (if they are kept),
-// with one barrier a group: 37 instructions a block in the chain. The arithmetic is the block
-// kernel's (alif_blocks_impl.h), operation by operation, so spikes and carries are the same bits.
-// Forward call, us, against the one-wave form: 1 x 100 x 1000: T_R 2 99 -> 49, T_R 4 77 -> 44;
-// 1 x 600 x 20000: T_R 2 1853 -> 874, T_R 3 1473 -> 816, T_R 4 1376 -> 756; with carries kept
-// 4 x 2048 x 3000, T_R 2: 289 -> 144. A block takes 0.087 us at T_R 2, about 190 cycles.
+// with one barrier a group. The arithmetic is the block kernel's (alif_blocks_impl.h),
+// operation by operation and segment by segment, so spikes and carries are the same bits.
+// us a block, block kernel / this one (1 x 100 x 8000): T_R 2 0.20 / 0.082, 4 0.31 / 0.152,
+// 5 0.45 / 0.18, 8 0.49 / 0.23, 10 0.42 / 0.27, 16 0.46 / 0.36, 20 0.51 / 0.41, 28 0.64 / 0.53,
+// 32 0.66 / 0.59; above, eight waves on a block are faster than one.
+#include <type_traits>
+
 #include "alif_common.h"
 #include "alif_kernels.h"
 
 namespace alif {
 namespace {
 
-constexpr int FC_G = 8;   // blocks a group (one barrier each)
 constexpr int FC_P = 3;   // groups of input in registers
 
-template <int L, int SDT>
+template <int TR>
 __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
-    constexpr uint32_t SB = SDT == 0 ? 1u : (SDT == 1 ? 2u : 4u);
-    __shared__ float in[2][FC_G][L][64];
-    __shared__ uint4 out[2][FC_G][64];   // carry-in v, a; spike step (0: none)
+    constexpr BlockConfig cfg = block_config(TR);
+    constexpr int L = cfg.len, SEG = (TR + L - 1) / L;   // segments with a step in them
+    constexpr int FC_G = TR <= 3 ? 16 : TR <= 4 ? 8 : TR <= 8 ? 4 : 2;  // blocks a group (one barrier each)
+    constexpr bool TAB = TR > 4;                         // powers of p in LDS
+    __shared__ float in[2][FC_G][TR][64];
+    __shared__ float2 out[2][FC_G][64];   // carry-in v, a
+    __shared__ uint8_t ots[2][FC_G][64];  // spike step (0: none)
+    __shared__ double ptab[TAB ? 64 * TR : 1];
     const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int work = xcd_remap(blockIdx.x, gridDim.x);
     const int b = work / a.n_groups, g = work - b * a.n_groups;
@@ -45,6 +52,8 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
     const size_t CO = b * CN + (size_t)a.ck_off * N;
     const bool ck = a.ck.v != nullptr;
     const double lb = -a.dt / (double)a.tau_m[nc], lp = -a.dt / (double)a.tau_a[nc];
+    if constexpr (TAB)   // (each lane's neuron is its own in every wave)
+        for (int k = role; k < TR; k += blockDim.x >> 6) ptab[lane * TR + k] = exp(lp * (double)k);
 
     // Rows go into the scalar offset, which the buffer's range check leaves out: they are
     // kept in range here, and lanes past N are out of range by their own offset.
@@ -53,22 +62,34 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
         const float bias = a.bias_k ? a.bias_k[nc] : 0.0f;
         const float omb = (float)(-expm1(lb)), ob = (float)(-expm1(lb) * (double)bias);
         const uint32_t n4 = (uint32_t)nc * 4u;
-        float x[FC_P][FC_G][L];
-        auto load = [&](float (&d)[FC_G][L], int q) __attribute__((always_inline)) {
+        float x[FC_P][FC_G * TR];
+        constexpr int ROWS = FC_G * TR;
+        const uint32_t step = (uint32_t)N * 4u;
+        // (a group past the last whole one: rows clamped, and no input past the end)
+        auto load = [&](float (&d)[ROWS], int q) __attribute__((always_inline)) {
+            const int t0 = q * ROWS;
+            if (t0 + ROWS <= T) {   // uniform
+                uint32_t row = (uint32_t)t0 * step;
 #pragma unroll
-            for (int i = 0; i < FC_G; i++)
+                for (int i = 0; i < ROWS; i++, row += step)
+                    d[i] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rI, n4, row, 0));
+            } else {
 #pragma unroll
-                for (int k = 0; k < L; k++)
-                    d[i][k] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                        rI, n4, (uint32_t)(min((q * FC_G + i) * L + k, T - 1) * N) * 4u, 0));
+                for (int i = 0; i < ROWS; i++)
+                    d[i] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                        rI, n4, (uint32_t)min(t0 + i, T - 1) * step, 0));
+            }
         };
-        auto put = [&](const float (&d)[FC_G][L], int q) __attribute__((always_inline)) {
-            const int t0 = q * FC_G * L;
+        auto put = [&](const float (&d)[ROWS], int q) __attribute__((always_inline)) {
+            float (&o)[FC_G][TR][64] = in[q & 1];
+            const int left = T - q * ROWS;
+            if (left >= ROWS) {
 #pragma unroll
-            for (int i = 0; i < FC_G; i++)
+                for (int i = 0; i < ROWS; i++) o[i / TR][i % TR][lane] = fmaf(omb, d[i], ob);
+            } else {
 #pragma unroll
-                for (int k = 0; k < L; k++)   // (no input past the end of a ragged last block)
-                    in[q & 1][i][k][lane] = fmaf(omb, t0 + i * L + k < T ? d[i][k] : 0.0f, ob);
+                for (int i = 0; i < ROWS; i++) o[i / TR][i % TR][lane] = fmaf(omb, i < left ? d[i] : 0.0f, ob);
+            }
         };
 #pragma unroll
         for (int p = 0; p < FC_P; p++) load(x[p], p);
@@ -78,38 +99,46 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
         for (int it = 0; it < iters; it += FC_P) {
 #pragma unroll
             for (int p = 0; p < FC_P; p++) {
-                const int q = it + p + 1;   // (past the last group: not read)
+                const int q = it + p + 1;   // (past the last group: not used)
                 put(x[(p + 1) % FC_P], q);
                 load(x[(p + 1) % FC_P], q + FC_P);
                 __syncthreads();
             }
         }
     } else if (role == 2) {
+        const int sdt = a.spike_dtype;
+        const uint32_t SB = sdt == 0 ? 1u : (sdt == 1 ? 2u : 4u), step = (uint32_t)N * SB;
         const rsrc_t rS = make_rsrc((const char *)a.spikes + b * bss * SB, (uint32_t)(TN * SB));
         const uint32_t ns = valid ? (uint32_t)n * SB : ALIF_OOB;
-        auto put = [&](uint32_t row, bool s) __attribute__((always_inline)) {
-            if constexpr (SDT == 0) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)s, rS, ns, row, 0);
-            else if constexpr (SDT == 1) __builtin_amdgcn_raw_buffer_store_b16(s ? (uint16_t)0x3F80 : (uint16_t)0, rS, ns, row, 0);
-            else __builtin_amdgcn_raw_buffer_store_b32(s ? 0x3F800000u : 0u, rS, ns, row, 0);
-        };
-        const uint32_t step = (uint32_t)N * SB;
         uint32_t row = 0;   // the group's first
         __syncthreads();
         for (int it = 0; it < iters; it++) {
             if (it > 0 && it <= groups) {
                 int ts[FC_G];
 #pragma unroll
-                for (int i = 0; i < FC_G; i++) ts[i] = (int)out[(it - 1) & 1][i][lane].z;
-                const int left = T - (it - 1) * FC_G * L;   // rows
-                if (left >= FC_G * L) {
+                for (int i = 0; i < FC_G; i++) ts[i] = ots[(it - 1) & 1][i][lane];
+                const int left = T - (it - 1) * FC_G * TR;   // rows
+                auto rows = [&](auto put) __attribute__((always_inline)) {
+                    if (left >= FC_G * TR) {
 #pragma unroll
-                    for (int i = 0; i < FC_G * L; i++) put(row + i * step, ts[i / L] == i % L + 1);
-                } else {
+                        for (int i = 0; i < FC_G * TR; i++) put(row + i * step, ts[i / TR] == i % TR + 1);
+                    } else {
 #pragma unroll
-                    for (int i = 0; i < FC_G * L; i++)
-                        if (i < left) put(row + i * step, ts[i / L] == i % L + 1);
-                }
-                row += FC_G * L * step;
+                        for (int i = 0; i < FC_G * TR; i++)
+                            if (i < left) put(row + i * step, ts[i / TR] == i % TR + 1);
+                    }
+                };
+                if (sdt == 0)
+                    rows([&](uint32_t r, bool s) { __builtin_amdgcn_raw_buffer_store_b8((uint8_t)s, rS, ns, r, 0); });
+                else if (sdt == 1)
+                    rows([&](uint32_t r, bool s) {
+                        __builtin_amdgcn_raw_buffer_store_b16(s ? (uint16_t)0x3F80 : (uint16_t)0, rS, ns, r, 0);
+                    });
+                else
+                    rows([&](uint32_t r, bool s) {
+                        __builtin_amdgcn_raw_buffer_store_b32(s ? 0x3F800000u : 0u, rS, ns, r, 0);
+                    });
+                row += FC_G * TR * step;
             }
             __syncthreads();
         }
@@ -118,25 +147,29 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
         const rsrc_t rCt = make_rsrc(a.ck.ts + CO, (uint32_t)CE);
         const uint32_t n4 = valid ? (uint32_t)n * 4u : ALIF_OOB, n1 = valid ? (uint32_t)n : ALIF_OOB;
         uint32_t e = 0;   // row of the group's first carry
-        auto put = [&](uint32_t e, uint4 r) __attribute__((always_inline)) {
-            __builtin_amdgcn_raw_buffer_store_b32(r.x, rCv, n4, e * 4u, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(r.y, rCa, n4, e * 4u, 0);
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)r.z, rCt, n1, e + (uint32_t)N, 0);
+        auto put = [&](uint32_t e, float2 r, uint8_t ts) __attribute__((always_inline)) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r.x), rCv, n4, e * 4u, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r.y), rCa, n4, e * 4u, 0);
+            __builtin_amdgcn_raw_buffer_store_b8(ts, rCt, n1, e + (uint32_t)N, 0);
         };
         __syncthreads();
         for (int it = 0; it < iters; it++) {
             if (it > 0 && it <= groups) {
-                uint4 r[FC_G];
+                float2 r[FC_G];
+                uint8_t ts[FC_G];
 #pragma unroll
-                for (int i = 0; i < FC_G; i++) r[i] = out[(it - 1) & 1][i][lane];
+                for (int i = 0; i < FC_G; i++) {
+                    r[i] = out[(it - 1) & 1][i][lane];
+                    ts[i] = ots[(it - 1) & 1][i][lane];
+                }
                 const int left = NB - (it - 1) * FC_G;
                 if (left >= FC_G) {
 #pragma unroll
-                    for (int i = 0; i < FC_G; i++) put(e + (uint32_t)(i * N), r[i]);
+                    for (int i = 0; i < FC_G; i++) put(e + (uint32_t)(i * N), r[i], ts[i]);
                 } else {
 #pragma unroll
                     for (int i = 0; i < FC_G; i++)
-                        if (i < left) put(e + (uint32_t)(i * N), r[i]);
+                        if (i < left) put(e + (uint32_t)(i * N), r[i], ts[i]);
                 }
                 e += (uint32_t)(FC_G * N);
             }
@@ -146,15 +179,20 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
         const float dd = a.d[nc], th0 = a.theta0[nc];
         if (valid && !params_ok(a.tau_m[n], a.tau_a[n], dd, th0)) atomicOr(a.status, 1u);
         const float beta = (float)exp(lb), pf = (float)exp(lp);
-        const double betaT = exp(lb * L), pT = exp(lp * L), pTm1 = exp(lp * (L - 1));
-        float bk[L], pt[L];
-        double pd[L];   // p^k
+        const double betaT = exp(lb * TR), pT = exp(lp * TR), pTm1 = exp(lp * (TR - 1));
+        float bk[L], pt[TR], bsL[SEG];   // beta^(k + 1); p^t; beta^(first step of the segment)
+        double pd[TAB ? 1 : TR];         // p^k
+        const float bL = (float)exp(lb * (double)L);
+        const float bPart = (float)exp(lb * (double)(TR - TR / L * L));   // over a partial segment
 #pragma unroll
-        for (int k = 0; k < L; k++) {
-            bk[k] = (float)exp(lb * (double)(k + 1));
-            pt[k] = (float)exp(lp * (double)k);
-            pd[k] = exp(lp * (double)k);
-        }
+        for (int k = 0; k < L; k++) bk[k] = (float)exp(lb * (double)(k + 1));
+#pragma unroll
+        for (int k = 0; k < TR; k++) pt[k] = (float)exp(lp * (double)k);
+#pragma unroll
+        for (int s = 0; s < SEG; s++) bsL[s] = (float)exp(lb * (double)(s * L));
+        if constexpr (!TAB)
+#pragma unroll
+            for (int k = 0; k < TR; k++) pd[k] = exp(lp * (double)k);
         double v0 = 0.0, a0 = 0.0;
         int cts = 0;
         if (a.init_v && valid) {
@@ -162,69 +200,107 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
             v0 = a.init_v[i];
             a0 = a.init_a[i];
             cts = a.init_ts[i];
-            if (cts < 0 || cts > L) {
+            if (cts < 0 || cts > TR) {
                 atomicOr(a.status, 1u);
                 cts = 0;
             }
         }
         if (ck && valid) a.ck.ts[CO + n] = (uint8_t)cts;
-        float cv = (float)v0, da1 = dd * fmaf(pf, (float)a0, cts == L ? 1.0f : 0.0f);
-        // The carry for every place the spike can be in, before the comparison that tells:
-        // what follows it is a selection, so the chain from one block's comparison to the
-        // next's does not run through the FP64 adaptation.
-        auto block = [&](const float (&x)[L], uint4 &o) __attribute__((always_inline)) {
-            float uu[L];
+        float cv = (float)v0, da1 = dd * fmaf(pf, (float)a0, cts == TR ? 1.0f : 0.0f);
+        auto block = [&](const float (&x)[TR], float2 &o, uint8_t &ot) __attribute__((always_inline)) {
+            // each segment's steps from its start (Prop. 1), the first cts - 1 masked
+            float uu[TR];
+            auto scan = [&](auto masked) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k < L; k++) {
-                const float d = k < L - 1 && cts > k + 1 ? 0.0f : x[k];   // masked refractory steps
-                uu[k] = k == 0 ? d : fmaf(beta, uu[k > 0 ? k - 1 : 0], d);
+                for (int t = 0; t < TR; t++) {
+                    const float d = decltype(masked)::value && t < TR - 1 && cts > t + 1 ? 0.0f : x[t];
+                    uu[t] = t % L == 0 ? d : fmaf(beta, uu[t > 0 ? t - 1 : 0], d);
+                }
+            };
+            if constexpr (TAB) {
+                if (__any(cts > 1)) scan(std::true_type{});
+                else scan(std::false_type{});
+            } else {
+                scan(std::true_type{});
             }
-            const double e1 = cts == L ? pTm1 : 0.0;
-            double an[L];    // a after: no spike or one in the last step; a spike in step 1, 2, ...
-            float dn[L + 1]; // a[1] of the next block: no spike; a spike in step 1, 2, ..., L
-            an[0] = fma(pT, a0, e1);
+            // the membrane's input part at each segment's start, V~ there, and at the block end
+            float C[SEG], u = uu[L - 1];
+            C[0] = cv;
 #pragma unroll
-            for (int k = 1; k < L; k++) an[k] = fma(pT, a0, e1 + pd[L - 1 - k]);
-#pragma unroll
-            for (int k = 0; k < L; k++) dn[k] = fmaf(pf, (float)an[k], 0.0f);
-            dn[L] = fmaf(pf, (float)an[0], 1.0f);
-            const double vn = fma(betaT, v0, (double)uu[L - 1]);
-            o = make_uint4(__float_as_uint(cv), __float_as_uint((float)a0), 0u, 0u);
+            for (int s = 1; s < SEG; s++) {
+                C[s] = fmaf(bsL[s], cv, u);
+                u = fmaf((s + 1) * L <= TR ? bL : bPart, u, uu[(s + 1) * L <= TR ? s * L + L - 1 : TR - 1]);
+            }
+            const double e1 = cts == TR ? pTm1 : 0.0;
+            double vn;
+            o = make_float2(cv, (float)a0);
             int ts = 0;   // the first step above threshold
             bool spk = false;
-            double as = an[0];
-            float ds = dn[0];
+            auto above = [&](int t) __attribute__((always_inline)) {
+                return fmaf(bk[t % L], C[t / L], uu[t]) > fmaf(pt[t], da1, th0);
+            };
+            if constexpr (!TAB) {
+                // The carry for every place the spike can be in, before the comparison that tells:
+                // what follows it is a selection, so the chain from one block's comparison to the
+                // next's does not run through the FP64 adaptation.
+                double an[TR];     // a after: no spike or one in the last step; a spike in step 1, 2, ...
+                float dn[TR + 1];  // a[1] of the next block: no spike; a spike in step 1, 2, ..., T_R
+                an[0] = fma(pT, a0, e1);
 #pragma unroll
-            for (int k = L - 1; k >= 0; k--) {
-                const bool c = fmaf(bk[k], cv, uu[k]) > fmaf(pt[k], da1, th0);
-                ts = c ? k + 1 : ts;
-                as = c ? an[k == L - 1 ? 0 : k + 1] : as;
-                ds = c ? dn[k + 1] : ds;
-                spk |= c;
+                for (int k = 1; k < TR; k++) an[k] = fma(pT, a0, e1 + pd[TR - 1 - k]);
+#pragma unroll
+                for (int k = 0; k < TR; k++) dn[k] = fmaf(pf, (float)an[k], 0.0f);
+                dn[TR] = fmaf(pf, (float)an[0], 1.0f);
+                vn = fma(betaT, v0, (double)u);
+                double as = an[0];
+                float ds = dn[0];
+#pragma unroll
+                for (int k = TR - 1; k >= 0; k--) {
+                    const bool c = above(k);
+                    ts = c ? k + 1 : ts;
+                    as = c ? an[k == TR - 1 ? 0 : k + 1] : as;
+                    ds = c ? dn[k + 1] : ds;
+                    spk |= c;
+                }
+                a0 = as;
+                da1 = dd * ds;
+            } else {
+                vn = fma(betaT, v0, (double)u);
+#pragma unroll
+                for (int k = TR - 1; k >= 0; k--) ts = above(k) ? k + 1 : ts;
+                spk = ts > 0;
+                const double an = fma(pT, a0, e1);
+                if (__any(spk)) {
+                    const double e2 = ptab[lane * TR + (spk ? max(TR - 1 - ts, 0) : 0)];
+                    const double as = fma(pT, a0, e1 + (ts < TR ? e2 : 0.0));
+                    a0 = spk ? as : an;
+                } else {
+                    a0 = an;
+                }
+                da1 = dd * fmaf(pf, (float)a0, ts == TR ? 1.0f : 0.0f);
             }
-            o.z = (uint32_t)ts;
+            ot = (uint8_t)ts;
             v0 = spk ? 0.0 : vn;
             cv = spk ? 0.0f : (float)vn;
-            a0 = as;
-            da1 = dd * ds;
             cts = ts;
         };
+        __builtin_amdgcn_s_setprio(3);   // (the other waves have time)
         __syncthreads();
         for (int it = 0; it < iters; it++) {
             const int nb0 = it * FC_G;
             if (nb0 < NB) {
-                float x[FC_G][L];
+                float x[FC_G][TR];
 #pragma unroll
                 for (int i = 0; i < FC_G; i++)
 #pragma unroll
-                    for (int k = 0; k < L; k++) x[i][k] = in[it & 1][i][k][lane];
+                    for (int k = 0; k < TR; k++) x[i][k] = in[it & 1][i][k][lane];
                 if (nb0 + FC_G <= NB) {
 #pragma unroll
-                    for (int i = 0; i < FC_G; i++) block(x[i], out[it & 1][i][lane]);
+                    for (int i = 0; i < FC_G; i++) block(x[i], out[it & 1][i][lane], ots[it & 1][i][lane]);
                 } else {
 #pragma unroll
                     for (int i = 0; i < FC_G; i++)
-                        if (nb0 + i < NB) block(x[i], out[it & 1][i][lane]);
+                        if (nb0 + i < NB) block(x[i], out[it & 1][i][lane], ots[it & 1][i][lane]);
                 }
             }
             __syncthreads();
@@ -246,12 +322,15 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
 
 }  // namespace
 
-// The chain pays while its card is not full: more groups than about two and a half a CU with
-// carries kept, four without, and the block kernel's 256 neurons a workgroup write their rows
-// in wider pieces. T_R 2, us, block kernel / this one: 768 groups 118 / 121 with carries, 107 / 65
-// without; 1024 groups 138 / 165 and 112 / 70; 2048 groups (T 2000) 577 / 694 and 311 / 356.
+// The chain pays while the card is not full: up to two and a half groups of 64 neurons a CU with
+// carries kept, four without (less where the LDS of a workgroup or its registers allow fewer at a
+// time); above, the block kernel's waves hide each other's latency and 256 neurons a workgroup
+// write rows in wider pieces. us, block kernel / this one: T_R 2: 768 groups 118 / 121 with
+// carries, 107 / 65 without; 1024 groups 138 / 165 and 112 / 70; T_R 20 without: 640 groups 55 / 42,
+// 1024 groups 77 / 74; T_R 28: 512 groups 48 / 37, 640 groups 61 / 69.
 bool fwd_chain_ok(int B, int N, int TR, bool traces, bool carries) {
-    return block_config(TR).seg == 1 && !traces && (long long)B * ((N + 63) / 64) <= (carries ? 640 : 1024);
+    const int most = TR > 24 ? 512 : carries ? 640 : TR == 3 ? 768 : 1024;
+    return TR <= 32 && !traces && (long long)B * ((N + 63) / 64) <= most;
 }
 
 hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st) {
@@ -259,16 +338,15 @@ hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st) {
     const unsigned grid = (unsigned)(a.B * a.n_groups);
     if (grid == 0) return hipSuccess;
     const dim3 blk(a.ck.v ? 256 : 192);
-#define ALIF_FC(L)                                                                                     \
-    do {                                                                                               \
-        if (a.spike_dtype == 0) hipLaunchKernelGGL((k_fwd_chain<L, 0>), dim3(grid), blk, 0, st, a);    \
-        else if (a.spike_dtype == 1) hipLaunchKernelGGL((k_fwd_chain<L, 1>), dim3(grid), blk, 0, st, a); \
-        else hipLaunchKernelGGL((k_fwd_chain<L, 2>), dim3(grid), blk, 0, st, a);                       \
-    } while (0)
-    if (a.TR == 2) ALIF_FC(2);
-    else if (a.TR == 3) ALIF_FC(3);
-    else ALIF_FC(4);
+    switch (a.TR) {
+#define ALIF_FC(TR) case TR: hipLaunchKernelGGL((k_fwd_chain<TR>), dim3(grid), blk, 0, st, a); break;
+        ALIF_FC(2) ALIF_FC(3) ALIF_FC(4) ALIF_FC(5) ALIF_FC(6) ALIF_FC(7) ALIF_FC(8) ALIF_FC(9) ALIF_FC(10)
+        ALIF_FC(11) ALIF_FC(12) ALIF_FC(13) ALIF_FC(14) ALIF_FC(15) ALIF_FC(16) ALIF_FC(17) ALIF_FC(18) ALIF_FC(19)
+        ALIF_FC(20) ALIF_FC(21) ALIF_FC(22) ALIF_FC(23) ALIF_FC(24) ALIF_FC(25) ALIF_FC(26) ALIF_FC(27) ALIF_FC(28)
+        ALIF_FC(29) ALIF_FC(30) ALIF_FC(31) ALIF_FC(32)
 #undef ALIF_FC
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -133,7 +133,27 @@ struct FinalizeArgs {
 struct BlockConfig {
     int seg, len;
 };
-BlockConfig block_config(int TR);
+constexpr BlockConfig block_config(int TR) {
+    if (TR <= 2) return {1, 2};
+    if (TR == 3) return {1, 3};
+    if (TR == 4) return {1, 4};
+    if (TR <= 6) return {2, 3};
+    if (TR <= 8) return {2, 4};
+    if (TR <= 12) return {4, 3};
+    if (TR <= 16) return {4, 4};
+    if (TR <= 20) return {4, 5};
+    if (TR <= 24) return {4, 6};
+    if (TR <= 32) return {4, 8};
+    if (TR <= 40) return {8, 5};
+    if (TR <= 48) return {8, 6};
+    if (TR <= 64) return {8, 8};
+    if (TR <= 80) return {8, 10};
+    if (TR <= 96) return {8, 12};
+    if (TR <= 104) return {8, 13};
+    if (TR <= 112) return {8, 14};
+    if (TR <= 120) return {8, 15};
+    return {8, 16};
+}
 int block_neurons_per_wg(int seg);
 
 hipError_t launch_blocks_fwd(const FwdArgs &a, hipStream_t st);
@@ -173,7 +193,7 @@ hipError_t launch_transpose(int N, const float *in, float *out, hipStream_t st);
 // skip_cnt set the kernel returns at entry when *skip_cnt <= skip_le as it starts
 hipError_t launch_shift_time(int B, int T, int N, int D, int elem, const void *in, void *out, hipStream_t st,
                              const unsigned long long *skip_cnt = nullptr, unsigned long long skip_le = 0);
-// blocks of one segment (T_R 2-4) without traces (alif_fwd_chain.hip): same bits; which calls
+// the forward without traces where the card is not full (alif_fwd_chain.hip): same bits; which calls
 bool fwd_chain_ok(int B, int N, int TR, bool traces, bool carries);
 hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st);
 hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
