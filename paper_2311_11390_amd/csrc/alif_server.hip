@@ -29,7 +29,14 @@
 // The linear recurrence is evaluated in chunks of OU_CHUNK steps: a first pass
 // gives each chunk's end value started from zero, a second pass combines the
 // ends of the earlier chunks into the chunk's start value and regenerates the
-// chunk's normals to write I.
+// chunk's normals to write I (storing them would move 16 bytes a step where the
+// result is 4). In both, OU_PARTS waves share a chunk of 64 neurons, a part each.
+//
+// What bounds it: arithmetic, ten rounds of two 32 x 32 -> 64 bit products (quarter
+// rate) and the FP64 logarithm, root, sine and cosine for every four normals, made
+// twice. So the elementary functions are those of the arguments that occur: -2 ln u of
+// a whole number by the odd series of ln((1 + s) / (1 - s)), the angle reduced exactly
+// as an integer, sine and cosine by their Taylor series on [-pi/4, pi/4].
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -62,71 +69,150 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1
     constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;   // Weyl key increments
 #pragma unroll
     for (int r = 0; r < 10; r++) {
-        const uint32_t hi0 = __umulhi(M0, c.x), lo0 = M0 * c.x;
-        const uint32_t hi1 = __umulhi(M1, c.z), lo1 = M1 * c.z;
-        c = u32x4{hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0};
+        const uint64_t p0 = (uint64_t)M0 * c.x, p1 = (uint64_t)M1 * c.z;
+        c = u32x4{(uint32_t)(p1 >> 32) ^ c.y ^ k0, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c.w ^ k1, (uint32_t)p0};
         k0 += W0;
         k1 += W1;
     }
     return c;
 }
 
+// sqrt(-2 ln((w + 1) / 2^32)). With w + 1 = m 2^k, m in [sqrt(1/2), sqrt(2)), f = m - 1 and
+// s = f / (2 + f): ln m = 2 s + 2 s^3 / 3 + 2 s^5 / 5 + ... = f - s (f - R), R = 2 s^2 / 3 +
+// 2 s^4 / 5 + ..., |s| < 0.1716: the first term left out is below 2^-57 of the sum. Where
+// k = 32 there is nothing to cancel, elsewhere |ln m| is at most half the rest.
+__device__ __forceinline__ double ou_radius(uint32_t w) {
+    const double u = (double)w + 1.0;
+    double m = __builtin_amdgcn_frexp_mant(u);
+    int k = __builtin_amdgcn_frexp_exp(u);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    k = low ? k - 1 : k;
+    const double f = m - 1.0, d = f + 2.0;
+    double y = __builtin_amdgcn_rcp(d);   // (to about half the bits: two Newton steps)
+    y = fma(y, fma(-d, y, 1.0), y);
+    y = fma(y, fma(-d, y, 1.0), y);
+    const double s = f * y, z = s * s;
+    double R = 2.0 / 21;
+#pragma unroll
+    for (int i = 19; i >= 3; i -= 2) R = fma(R, z, 2.0 / i);
+    const double lnm = f - s * fma(-R, z, f);
+    const double x = -2.0 * fma((double)(k - 32), 0.69314718055994530942, lnm);
+    // sqrt: the hardware's estimate of 1 / sqrt(x), two coupled Newton steps and a last correction
+    double r = __builtin_amdgcn_rsq(x), g = x * r, h = 0.5 * r;
+    r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+
+// cos and sin of 2 pi w / 2^32: the nearest quarter turn taken off w exactly
+__device__ __forceinline__ void ou_angle(uint32_t w, double &co, double &si) {
+    const uint32_t q = (w + 0x20000000u) >> 30;
+    const double x = (double)(int32_t)(w - (q << 30)) * (6.283185307179586476925 / 4294967296.0), z = x * x;
+    double c = 1.0 / 20922789888000.0, t = 1.0 / 355687428096000.0;   // 1 / 16!, 1 / 17!
+    c = fma(c, z, -1.0 / 87178291200.0);
+    t = fma(t, z, -1.0 / 1307674368000.0);
+    c = fma(c, z, 1.0 / 479001600.0);
+    t = fma(t, z, 1.0 / 6227020800.0);
+    c = fma(c, z, -1.0 / 3628800.0);
+    t = fma(t, z, -1.0 / 39916800.0);
+    c = fma(c, z, 1.0 / 40320.0);
+    t = fma(t, z, 1.0 / 362880.0);
+    c = fma(c, z, -1.0 / 720.0);
+    t = fma(t, z, -1.0 / 5040.0);
+    c = fma(c, z, 1.0 / 24.0);
+    t = fma(t, z, 1.0 / 120.0);
+    c = fma(c, z, -0.5);
+    t = fma(t, z, -1.0 / 6.0);
+    c = fma(c, z, 1.0);
+    t = fma(t * z, x, x);
+    const double p = q & 1 ? t : c, v = q & 1 ? c : t;
+    co = (q + 1) & 2 ? -p : p;
+    si = q & 2 ? -v : v;
+}
+
 // the four standard normals of steps 4q .. 4q + 3 of neuron n
 __device__ __forceinline__ void ou_normals4(uint64_t seed, int q, int n, double z[4]) {
     const u32x4 w = philox4x32_10(u32x4{(uint32_t)q, (uint32_t)n, 0u, 0u}, (uint32_t)seed,
                                   (uint32_t)(seed >> 32));
-    constexpr double INV32 = 1.0 / 4294967296.0, TWO_PI = 6.283185307179586476925;
-    const double r0 = sqrt(-2.0 * log(((double)w.x + 1.0) * INV32));
-    const double r1 = sqrt(-2.0 * log(((double)w.z + 1.0) * INV32));
-    const double a0 = TWO_PI * ((double)w.y * INV32), a1 = TWO_PI * ((double)w.w * INV32);
-    z[0] = r0 * cos(a0);
-    z[1] = r0 * sin(a0);
-    z[2] = r1 * cos(a1);
-    z[3] = r1 * sin(a1);
+    const double r0 = ou_radius(w.x), r1 = ou_radius(w.z);
+    double c0, s0, c1, s1;
+    ou_angle(w.y, c0, s0);
+    ou_angle(w.w, c1, s1);
+    z[0] = r0 * c0;
+    z[1] = r0 * s0;
+    z[2] = r1 * c1;
+    z[3] = r1 * s1;
 }
 
-constexpr int OU_CHUNK = 256;   // steps per chunk (a multiple of 4)
+constexpr int OU_CHUNK = 256;   // steps per chunk
+constexpr int OU_PARTS = 8;     // waves per chunk: a part's 32 normals stay in registers
+constexpr int OU_PART = OU_CHUNK / OU_PARTS;
 
 struct OuArgs {
     int T, N;
-    double e, s, sd, mu, eC;    // e = exp(-DT/tau), s = sd sqrt(1 - e^2), eC = e^OU_CHUNK
+    double e, s, sd, mu;        // e = exp(-DT/tau), s = sd sqrt(1 - e^2)
+    double eP, eC;              // e^OU_PART, e^OU_CHUNK
     uint64_t seed;
     double *ends;               // [NC][N]
     float *I;                   // [T][N]
 };
 
-// X over steps [t0, t1) of one chunk, starting from x (the value at t0 - 1)
-template <bool WRITE>
-__device__ __forceinline__ double ou_chunk(const OuArgs &a, int n, int t0, int t1, double x) {
-    for (int t = t0; t < t1; t += 4) {
-        double z[4];
-        ou_normals4(a.seed, t >> 2, n, z);
+// The noise terms of part `part` of chunk `ch` (X[0]'s is sd z) and X at its end from zero
+__device__ __forceinline__ double ou_part(const OuArgs &a, int n, int ch, int part, double (&z)[OU_PART]) {
+    const int t0 = ch * OU_CHUNK + part * OU_PART;
+    double x = 0.0;
+#pragma unroll
+    for (int i = 0; i < OU_PART; i += 4) {
+        double v[4];
+        ou_normals4(a.seed, (t0 + i) >> 2, n, v);
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            if (t + j >= t1) break;
-            x = (t + j == 0) ? a.sd * z[j] : fma(a.e, x, a.s * z[j]);
-            if constexpr (WRITE) a.I[(size_t)(t + j) * a.N + n] = (float)(a.mu + x);
+            z[i + j] = (t0 + i + j == 0 ? a.sd : a.s) * v[j];
+            x = fma(a.e, x, z[i + j]);
         }
     }
     return x;
 }
 
-__global__ void k_ou_chunk_ends(OuArgs a) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ch = blockIdx.y;
-    if (n >= a.N) return;
-    const int t0 = ch * OU_CHUNK, t1 = min(a.T, t0 + OU_CHUNK);
-    a.ends[(size_t)ch * a.N + n] = ou_chunk<false>(a, n, t0, t1, 0.0);
+// of the whole chunks that another follows
+__global__ void __launch_bounds__(64 * OU_PARTS) k_ou_chunk_ends(OuArgs a) {
+    __shared__ double end[OU_PARTS][64];
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int n = blockIdx.x * 64 + lane, ch = blockIdx.y;
+    double z[OU_PART];
+    end[part][lane] = ou_part(a, n, ch, part, z);
+    __syncthreads();
+    if (part != 0 || n >= a.N) return;
+    double x = 0.0;
+#pragma unroll
+    for (int p = 0; p < OU_PARTS; p++) x = fma(a.eP, x, end[p][lane]);
+    a.ends[(size_t)ch * a.N + n] = x;
 }
 
-__global__ void k_ou_fill(OuArgs a) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ch = blockIdx.y;
+__global__ void __launch_bounds__(64 * OU_PARTS) k_ou_fill(OuArgs a) {
+    __shared__ double end[OU_PARTS][64];
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int n = blockIdx.x * 64 + lane, ch = blockIdx.y;
+    double z[OU_PART];
+    end[part][lane] = ou_part(a, n, ch, part, z);
+    __syncthreads();
     if (n >= a.N) return;
-    double x = 0.0;   // X at the last step of chunk ch - 1
+    double x = 0.0;   // X at the last step before this part
     for (int c = 0; c < ch; c++) x = fma(a.eC, x, a.ends[(size_t)c * a.N + n]);
-    const int t0 = ch * OU_CHUNK, t1 = min(a.T, t0 + OU_CHUNK);
-    ou_chunk<true>(a, n, t0, t1, x);
+    for (int p = 0; p < part; p++) x = fma(a.eP, x, end[p][lane]);
+    const int t0 = ch * OU_CHUNK + part * OU_PART;
+    float *I = a.I + (size_t)t0 * a.N + n;
+#pragma unroll
+    for (int i = 0; i < OU_PART; i++) {
+        x = fma(a.e, x, z[i]);
+        if (t0 + i < a.T) I[(size_t)i * a.N] = (float)(a.mu + x);
+    }
 }
 
 size_t ou_chunks(int T) { return ((size_t)T + OU_CHUNK - 1) / OU_CHUNK; }
@@ -151,13 +237,14 @@ hipError_t ou_launch(int T, int N, double dt, float tau, float mean, float sd, u
     a.s = (double)sd * std::sqrt(1.0 - a.e * a.e);
     a.sd = sd;
     a.mu = mean;
+    a.eP = std::pow(a.e, (double)OU_PART);
     a.eC = std::pow(a.e, (double)OU_CHUNK);
     a.seed = seed;
     a.ends = ends;
     a.I = I;
-    const dim3 grid((unsigned)((N + 63) / 64), (unsigned)ou_chunks(T));
-    hipLaunchKernelGGL(k_ou_chunk_ends, grid, dim3(64), 0, st, a);
-    hipLaunchKernelGGL(k_ou_fill, grid, dim3(64), 0, st, a);
+    const unsigned cols = (unsigned)((N + 63) / 64), chunks = (unsigned)ou_chunks(T);
+    if (chunks > 1) hipLaunchKernelGGL(k_ou_chunk_ends, dim3(cols, chunks - 1), dim3(64 * OU_PARTS), 0, st, a);
+    hipLaunchKernelGGL(k_ou_fill, dim3(cols, chunks), dim3(64 * OU_PARTS), 0, st, a);
     return hipGetLastError();
 }
 
