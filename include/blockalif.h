@@ -548,10 +548,12 @@ typedef struct alif_result {
  * fits in what is left of hbm_budget_bytes, and runs each on its slot's own
  * stream on `device` (default priority), so that requests that arrive while
  * others run overlap on the GPU. A request's result does not depend on what
- * else is resident. 1 <= max_slots <= 64. Device memory for a request is taken
- * from HIP's stream-ordered allocator at admission and returned on completion;
- * each slot also keeps pinned host staging, grown to the largest request it
- * has served.
+ * else is resident. 1 <= max_slots <= 64. The device memory of a finished
+ * request is kept for later ones that it fits (a request may get a block up to
+ * an eighth larger than its footprint while half of the budget is free); all that
+ * the server holds stays within hbm_budget_bytes and goes back to the device after
+ * a second without requests, and with the server. Each slot also keeps pinned host
+ * staging, grown to the largest request it has served.
  */
 int alif_server_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t device,
                        alif_server **out);
