@@ -93,32 +93,52 @@ __device__ __forceinline__ int nz_elems(uint32_t v) {
     else return (v & 0x7fffffffu) != 0u;
 }
 
+// What bounds it: latency, in one workgroup. The rows' addresses take two 64-bit divisions
+// each, so they are computed a row a thread and handed out through LDS, and a wave has the
+// loads of four rows in flight (13 -> 6 us on 32000 x 700 bytes, 18 -> 9 us on 131072 x 200).
 template <int ELEM, bool VEC>
 __global__ __launch_bounds__(1024) void k_wg_sample(WgArgs a) {
+    constexpr int ROWS = 4, STEPS = 4;   // rows and loads of a row in flight
     __shared__ int part[16];
+    __shared__ long long first[1024];    // a batch's rows: their first elements
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long R = (long long)a.B * a.TD;   // source rows
     const long long want = SROWS > (SAMPLE + a.Nj - 1) / a.Nj ? SROWS : (SAMPLE + a.Nj - 1) / a.Nj;
     const long long taken = R < want ? R : want;
+    const int units = VEC ? a.Nj * ELEM / 4 : a.Nj;   // loads of a row
     int c = 0;
-#pragma unroll 4
-    for (long long k = wave; k < taken; k += 16) {   // (uniform per wave)
-        const long long r = k * R / taken;
-        const long long b = r / a.TD, u = r - b * a.TD;
-        const char *row = static_cast<const char *>(a.spikes) + ((size_t)b * a.T + (size_t)u) * a.Nj * ELEM;
-        if constexpr (VEC) {
-            const int words = a.Nj * ELEM / 4;
-#pragma unroll 4
-            for (int w = lane; w < words; w += 64) c += nz_elems<ELEM>(reinterpret_cast<const uint32_t *>(row)[w]);
-        } else {
-#pragma unroll 4
-            for (int j = lane; j < a.Nj; j += 64) {
-                uint32_t v;
-                if constexpr (ELEM == 1) v = reinterpret_cast<const uint8_t *>(row)[j];
-                else v = (uint32_t)reinterpret_cast<const uint16_t *>(row)[j];   // (unaligned float rows take VEC)
-                c += nz_elems<ELEM>(v);
-            }
+    for (long long k0 = 0; k0 < taken; k0 += 1024) {
+        const int rows = (int)(taken - k0 < 1024 ? taken - k0 : 1024);
+        __syncthreads();
+        if ((int)threadIdx.x < rows) {
+            const long long r = (k0 + threadIdx.x) * R / taken;
+            const long long b = r / a.TD, u = r - b * a.TD;
+            first[threadIdx.x] = (b * a.T + u) * a.Nj;
         }
+        __syncthreads();
+        for (int i0 = wave; i0 < rows; i0 += 16 * ROWS)   // (uniform per wave)
+            for (int w0 = lane; w0 < units; w0 += 64 * STEPS) {
+                uint32_t v[ROWS][STEPS];
+#pragma unroll
+                for (int i = 0; i < ROWS; i++) {
+                    const int row = i0 + 16 * i;
+                    const char *p = static_cast<const char *>(a.spikes) + first[row < rows ? row : i0] * ELEM;
+#pragma unroll
+                    for (int s = 0; s < STEPS; s++) {
+                        const int w = w0 + 64 * s;
+                        v[i][s] = 0u;
+                        if (row < rows && w < units) {
+                            if constexpr (VEC) v[i][s] = reinterpret_cast<const uint32_t *>(p)[w];
+                            else if constexpr (ELEM == 1) v[i][s] = reinterpret_cast<const uint8_t *>(p)[w];
+                            else v[i][s] = reinterpret_cast<const uint16_t *>(p)[w];   // (unaligned float rows take VEC)
+                        }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < ROWS; i++)
+#pragma unroll
+                    for (int s = 0; s < STEPS; s++) c += nz_elems<ELEM>(v[i][s]);
+            }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
