@@ -4,7 +4,7 @@
 // each operand is read either k-contiguous or m/n-contiguous and may be float,
 // uint8 (0/1 spikes) or bfloat16. A 256-thread workgroup owns a 128 x 128 tile
 // of C; its four waves each own 64 x 64 as 4 x 4 MFMA 16 x 16 accumulators.
-// K is staged through LDS 16 (FP32) or 32 (BF16) at a time.
+// K is staged through LDS 16 (FP32) or 32 (BF16) at a time (the general kernel).
 //   FP32: v_mfma_f32_16x16x4_f32, operands rounded nowhere.
 //   BF16: operands rounded to bfloat16 (0/1 spikes exactly), v_mfma_f32_16x16x32_bf16,
 //         FP32 accumulation.
@@ -134,7 +134,9 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 //   row-contiguous operand ([k][row] in memory): a thread loads RR consecutive
 //     rows for 8 consecutive k and transposes them in registers.
 // BF16 tiles are 256 x 128 over eight waves (the operand read as float is reused
-// over more rows), FP32 tiles 128 x 128 over four; each wave owns 64 x 64 as
+// over more rows), FP32 tiles 128 x 128 over four, 16 deep up to K 256 (four workgroups a
+// CU instead of two: 131072 x 256 from K 200 167 -> 143 us) and 32 above (fewer barriers:
+// 8000 x 512 from K 500 97 -> 95 us a layer's forward); each wave owns 64 x 64 as
 // 4 x 4 MFMA 16 x 16 accumulators. Workgroups are numbered so that the N tiles
 // of one M tile (and K split) run on one XCD and share its rows of A in that
 // XCD's L2. A split over K writes partial tiles that k_split_reduce sums.
@@ -142,13 +144,14 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 // k-contiguous), the input gradient (A = gI k-contiguous, B = W row-contiguous)
 // and the weight gradient (A = gI and B = spikes, both row-contiguous).
 // ---------------------------------------------------------------------------
-template <bool BF16>
+// PM: 1 BF16, 0 FP32, 2 FP32 with deep stages
+template <int PM>
 struct Tile {
-    static constexpr int BM = BF16 ? 256 : 128, BN = 128;
-    static constexpr int THREADS = BF16 ? 512 : 256;
-    static constexpr int BK = BF16 ? 64 : 32;           // k per stage
-    static constexpr int LDK = BF16 ? BK + 8 : BK + 4;   // LDS row (elements), 16-byte multiple
-    using T = typename std::conditional<BF16, __bf16, float>::type;
+    static constexpr int BM = PM == 1 ? 256 : 128, BN = 128;
+    static constexpr int THREADS = PM == 1 ? 512 : 256;
+    static constexpr int BK = PM == 1 ? 64 : PM == 2 ? 32 : 16;   // k per stage
+    static constexpr int LDK = PM == 1 ? BK + 8 : BK + 4;   // LDS row (elements), 16-byte multiple
+    using T = typename std::conditional<PM == 1, __bf16, float>::type;
     static constexpr size_t lds_bytes() { return (size_t)2 * (BM + BN) * LDK * sizeof(T); }
 };
 
@@ -202,37 +205,37 @@ struct Run {
 // MFMA fragment reads (16 consecutive rows, one chunk each) stay conflict-free
 // and the transposing stores of row-contiguous operands, whose lanes write rows
 // RR apart, spread over all banks instead of a quarter of them.
-template <bool BF16>
+template <int PM>
 __device__ __forceinline__ int lds_at(int row, int chunk) {
-    constexpr int CE = BF16 ? 8 : 4;
-    return row * Tile<BF16>::LDK + (chunk ^ ((row >> 4) & 3)) * CE;
+    constexpr int CE = PM == 1 ? 8 : 4;
+    return row * Tile<PM>::LDK + (chunk ^ ((row >> 4) & 3)) * CE;
 }
 
 // 4 values (k = 4 h .. 4 h + 3 of chunk c) to LDS row `row` in the MFMA operand type
-template <bool BF16>
-__device__ __forceinline__ void lds_store4(typename Tile<BF16>::T *buf, int row, int k, const float *v) {
-    if constexpr (BF16) {
+template <int PM>
+__device__ __forceinline__ void lds_store4(typename Tile<PM>::T *buf, int row, int k, const float *v) {
+    if constexpr (PM == 1) {
         typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
         bf16x4 q;
 #pragma unroll
         for (int e = 0; e < 4; e++) q[e] = (__bf16)v[e];
-        *reinterpret_cast<bf16x4 *>(buf + lds_at<true>(row, k >> 3) + (k & 4)) = q;
+        *reinterpret_cast<bf16x4 *>(buf + lds_at<PM>(row, k >> 3) + (k & 4)) = q;
     } else {
-        *reinterpret_cast<floatx4 *>(buf + lds_at<false>(row, k >> 2)) = floatx4{v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<floatx4 *>(buf + lds_at<PM>(row, k >> 2)) = floatx4{v[0], v[1], v[2], v[3]};
     }
 }
 
 // 8 values (k = k0 .. k0 + 7, k0 a multiple of 8) to LDS row `row`
-template <bool BF16>
-__device__ __forceinline__ void lds_store8(typename Tile<BF16>::T *buf, int row, int k0, const float *v) {
-    if constexpr (BF16) {
+template <int PM>
+__device__ __forceinline__ void lds_store8(typename Tile<PM>::T *buf, int row, int k0, const float *v) {
+    if constexpr (PM == 1) {
         bf16x8 q;
 #pragma unroll
         for (int e = 0; e < 8; e++) q[e] = (__bf16)v[e];
-        *reinterpret_cast<bf16x8 *>(buf + lds_at<true>(row, k0 >> 3)) = q;
+        *reinterpret_cast<bf16x8 *>(buf + lds_at<PM>(row, k0 >> 3)) = q;
     } else {
-        *reinterpret_cast<floatx4 *>(buf + lds_at<false>(row, k0 >> 2)) = floatx4{v[0], v[1], v[2], v[3]};
-        *reinterpret_cast<floatx4 *>(buf + lds_at<false>(row, (k0 >> 2) + 1)) = floatx4{v[4], v[5], v[6], v[7]};
+        *reinterpret_cast<floatx4 *>(buf + lds_at<PM>(row, k0 >> 2)) = floatx4{v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<floatx4 *>(buf + lds_at<PM>(row, (k0 >> 2) + 1)) = floatx4{v[4], v[5], v[6], v[7]};
     }
 }
 
@@ -252,9 +255,9 @@ __device__ __forceinline__ void lds_store8(typename Tile<BF16>::T *buf, int row,
 //   last stage;
 // row-contiguous: k >= ke reads 0; rows beyond the valid ones may read other
 //   data, which only reaches rows of C that are never stored.
-template <int DT, bool KM, int ROWS, bool BF16>
+template <int DT, bool KM, int ROWS, int PM>
 struct Stage {
-    using P = Tile<BF16>;
+    using P = Tile<PM>;
     static constexpr int BK = P::BK;
     static constexpr int EPT = ROWS * BK / P::THREADS;   // elements per thread per stage
     static constexpr int RR = EPT / 8;                    // row-contiguous: rows per thread
@@ -337,7 +340,7 @@ struct Stage {
                 float c[8];
 #pragma unroll
                 for (int j = 0; j < 8; j++) c[j] = v[j][rr];
-                lds_store8<BF16>(buf, lrow + rr, lk, c);
+                lds_store8<PM>(buf, lrow + rr, lk, c);
             }
         } else {
             float v[NI][4];
@@ -350,16 +353,16 @@ struct Stage {
                     for (int e = 0; e < 4; e++) v[i][e] = e < g.kmax ? v[i][e] : 0.0f;
             }
 #pragma unroll
-            for (int i = 0; i < NI; i++) lds_store4<BF16>(buf, lrow + i * RPP, lk, v[i]);
+            for (int i = 0; i < NI; i++) lds_store4<PM>(buf, lrow + i * RPP, lk, v[i]);
         }
     }
 };
 
-template <int ADT, bool AKM, int BDT, bool BKM, bool BF16>
-__global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, int m_tiles, int n_tiles,
+template <int ADT, bool AKM, int BDT, bool BKM, int PM>
+__global__ __launch_bounds__(Tile<PM>::THREADS) void k_gemm_tiled(GemmArgs g, int m_tiles, int n_tiles,
                                                                      int kps, int total) {
     if (gemm_gated_off(g.skip_cnt, g.skip_le)) return;
-    using P = Tile<BF16>;
+    using P = Tile<PM>;
     using T = typename P::T;
     constexpr int BM = P::BM, BN = P::BN, BK = P::BK, LDK = P::LDK;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -375,8 +378,8 @@ __global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;              // wave tile (wm, wn) of 64 x 64
 
-    Stage<ADT, AKM, BM, BF16> sa;
-    Stage<BDT, BKM, BN, BF16> sb;
+    Stage<ADT, AKM, BM, PM> sa;
+    Stage<BDT, BKM, BN, PM> sb;
     sa.init(g.A, g.lda, g.M, m0, kb, ke, tid);
     sb.init(g.B, g.ldb, g.N, n0, kb, ke, tid);
 
@@ -390,17 +393,17 @@ __global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, 
     auto mma = [&](int buf) {
         const T *a = As + (size_t)buf * BM * LDK;
         const T *b = Bs + (size_t)buf * BN * LDK;
-        if constexpr (BF16) {
+        if constexpr (PM == 1) {
 #pragma unroll
             for (int kq = 0; kq < BK; kq += 32) {
                 bf16x8 fa[4], fb[4];
                 const int kc = kq + 8 * (lane >> 4);
 #pragma unroll
                 for (int i = 0; i < 4; i++)
-                    fa[i] = *reinterpret_cast<const bf16x8 *>(a + lds_at<true>(wm * 64 + i * 16 + (lane & 15), kc >> 3));
+                    fa[i] = *reinterpret_cast<const bf16x8 *>(a + lds_at<PM>(wm * 64 + i * 16 + (lane & 15), kc >> 3));
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-                    fb[j] = *reinterpret_cast<const bf16x8 *>(b + lds_at<true>(wn * 64 + j * 16 + (lane & 15), kc >> 3));
+                    fb[j] = *reinterpret_cast<const bf16x8 *>(b + lds_at<PM>(wn * 64 + j * 16 + (lane & 15), kc >> 3));
 #pragma unroll
                 for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -413,9 +416,9 @@ __global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, 
                 const int kc = ks + (lane >> 4);
                 float fa[4], fb[4];
 #pragma unroll
-                for (int i = 0; i < 4; i++) fa[i] = a[lds_at<false>(wm * 64 + i * 16 + (lane & 15), kc >> 2) + (kc & 3)];
+                for (int i = 0; i < 4; i++) fa[i] = a[lds_at<PM>(wm * 64 + i * 16 + (lane & 15), kc >> 2) + (kc & 3)];
 #pragma unroll
-                for (int j = 0; j < 4; j++) fb[j] = b[lds_at<false>(wn * 64 + j * 16 + (lane & 15), kc >> 2) + (kc & 3)];
+                for (int j = 0; j < 4; j++) fb[j] = b[lds_at<PM>(wn * 64 + j * 16 + (lane & 15), kc >> 2) + (kc & 3)];
 #pragma unroll
                 for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -428,12 +431,12 @@ __global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, 
     // Loads are issued unconditionally (past the split they read zeros): a load
     // under a condition makes the compiler copy its registers, which waits for
     // it. sched_barrier keeps the compiler from moving instructions across it.
-    using SA = Stage<ADT, AKM, BM, BF16>;
-    using SB = Stage<BDT, BKM, BN, BF16>;
+    using SA = Stage<ADT, AKM, BM, PM>;
+    using SB = Stage<BDT, BKM, BN, PM>;
     T *const L0a = As, *const L1a = As + (size_t)BM * LDK;
     T *const L0b = Bs, *const L1b = Bs + (size_t)BN * LDK;
     const int nk = (ke - kb + BK - 1) / BK;
-    if constexpr (BF16 && SA::REG_WORDS + SB::REG_WORDS <= 32) {
+    if constexpr (PM == 1 && SA::REG_WORDS + SB::REG_WORDS <= 32) {
         // Two stages in flight. While stage kt is multiplied from one LDS
         // buffer, stage kt + 1, loaded a whole stage earlier, is converted and
         // stored to the other, interleaved with the MFMAs; then the loads of
@@ -511,6 +514,86 @@ __global__ __launch_bounds__(Tile<BF16>::THREADS) void k_gemm_tiled(GemmArgs g, 
     }
 }
 
+// Small products C = A B^T (+ bias), both k-contiguous, B float: a wave takes 16 TI x 16 TJ
+// of C straight from memory, by v_mfma_f32_16x16x4_f32 over increasing k as the tiled path
+// does (the same bits), a step of k per element load, so any alignment goes. The tiled path's
+// 128 x 128 tiles are 8 workgroups for 1000 x 100, a tile's stages in sequence.
+template <int ADT, int TI, int TJ>
+__global__ __launch_bounds__(256) void k_gemm_small(GemmArgs g, int n_tiles, long long total) {
+    if (gemm_gated_off(g.skip_cnt, g.skip_le)) return;
+    constexpr int U = TI * TJ == 1 ? 16 : 8;   // steps of 4 k in flight
+    const int lane = threadIdx.x & 63;
+    const long long work = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (work >= total) return;   // no barrier in this kernel
+    const long long m0 = work / n_tiles * (16 * TI);
+    const int n0 = (int)(work % n_tiles) * (16 * TJ), r = lane & 15, q = lane >> 4;
+    const char *pa[TI];
+    const float *pb[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; i++) {   // (rows past the end repeat the last one; their results are dropped)
+        const long long m = m0 + 16 * i + r;
+        pa[i] = static_cast<const char *>(g.A) + (m < g.M ? m : g.M - 1) * g.lda * elem_bytes<ADT>();
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; j++) pb[j] = static_cast<const float *>(g.B) + (long long)min(n0 + 16 * j + r, g.N - 1) * g.ldb;
+    floatx4 acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; i++)
+#pragma unroll
+        for (int j = 0; j < TJ; j++) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto at = [&](const char *p, int k) __attribute__((always_inline)) {
+        if constexpr (ADT == 0) return reinterpret_cast<const float *>(p)[k];
+        else if constexpr (ADT == 1) return (float)reinterpret_cast<const uint8_t *>(p)[k];
+        else return __uint_as_float((uint32_t) reinterpret_cast<const uint16_t *>(p)[k] << 16);
+    };
+    for (int k0 = q; k0 < g.K + q; k0 += 4 * U) {   // (uniform)
+        float fa[U][TI], fb[U][TJ];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int k = min(k0 + 4 * u, g.K - 1);
+            const bool in = k0 + 4 * u < g.K;
+#pragma unroll
+            for (int i = 0; i < TI; i++) fa[u][i] = at(pa[i], k);
+#pragma unroll
+            for (int j = 0; j < TJ; j++) fb[u][j] = pb[j][k];
+#pragma unroll
+            for (int i = 0; i < TI; i++) fa[u][i] = in ? fa[u][i] : 0.0f;
+#pragma unroll
+            for (int j = 0; j < TJ; j++) fb[u][j] = in ? fb[u][j] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int i = 0; i < TI; i++)
+#pragma unroll
+                for (int j = 0; j < TJ; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][i], fb[u][j], acc[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; j++) {
+        const int n = n0 + 16 * j + r;
+        const float bias = g.bias && n < g.N ? g.bias[n] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < TI; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const long long m = m0 + 16 * i + 4 * q + e;
+                if (m < g.M && n < g.N) g.C[m * g.ldc + n] = acc[i][j][e] + bias;
+            }
+    }
+}
+
+template <int TI, int TJ>
+static hipError_t small_launch(const GemmArgs &g, hipStream_t st) {
+    const int nt = (g.N + 16 * TJ - 1) / (16 * TJ);
+    const long long total = (g.M + 16 * TI - 1) / (16 * TI) * nt;
+    const dim3 grid((unsigned)((total + 3) / 4)), blk(256);
+    if (g.a_dt == 0) hipLaunchKernelGGL((k_gemm_small<0, TI, TJ>), grid, blk, 0, st, g, nt, total);
+    else if (g.a_dt == 1) hipLaunchKernelGGL((k_gemm_small<1, TI, TJ>), grid, blk, 0, st, g, nt, total);
+    else hipLaunchKernelGGL((k_gemm_small<2, TI, TJ>), grid, blk, 0, st, g, nt, total);
+    return hipGetLastError();
+}
+
 // K per split of the tiled path: a multiple of the stage depth
 static int tiled_kps(const GemmArgs &g, int bk) {
     const int s = g.splits < 1 ? 1 : g.splits;
@@ -522,8 +605,8 @@ static int tiled_kps(const GemmArgs &g, int bk) {
 // rows and bases aligned for its vector loads, every buffer extent within 31 bits
 static bool tiled_ok(const GemmArgs &g, bool bf16) {
     const bool fwd = g.a_kc && g.b_kc && g.b_dt == 0;
-    const bool dx = g.a_kc && (g.a_dt == 0 || g.a_dt == 2) && !g.b_kc && g.b_dt == 0;
-    const bool dw = !g.a_kc && (g.a_dt == 0 || g.a_dt == 2) && !g.b_kc;
+    const bool dx = bf16 && g.a_kc && (g.a_dt == 0 || g.a_dt == 2) && !g.b_kc && g.b_dt == 0;
+    const bool dw = bf16 && !g.a_kc && (g.a_dt == 0 || g.a_dt == 2) && !g.b_kc;
     if (!(fwd || dx || dw) || g.K <= 0) return false;
     if ((reinterpret_cast<uintptr_t>(g.A) & 15) || (reinterpret_cast<uintptr_t>(g.B) & 15)) return false;
     if (g.lda % 4 != 0 || g.ldb % 4 != 0) return false;
@@ -539,15 +622,15 @@ static bool tiled_ok(const GemmArgs &g, bool bf16) {
     return a_ext < lim && b_ext < lim;
 }
 
-template <int ADT, bool AKM, int BDT, bool BKM, bool BF16>
+template <int ADT, bool AKM, int BDT, bool BKM, int PM>
 static void tiled_go(const GemmArgs &g, int m_tiles, int n_tiles, int kps, int total, hipStream_t st) {
-    hipLaunchKernelGGL((k_gemm_tiled<ADT, AKM, BDT, BKM, BF16>), dim3((unsigned)total),
-                       dim3(Tile<BF16>::THREADS), Tile<BF16>::lds_bytes(), st, g, m_tiles, n_tiles, kps, total);
+    hipLaunchKernelGGL((k_gemm_tiled<ADT, AKM, BDT, BKM, PM>), dim3((unsigned)total),
+                       dim3(Tile<PM>::THREADS), Tile<PM>::lds_bytes(), st, g, m_tiles, n_tiles, kps, total);
 }
 
-template <bool BF16>
+template <int PM>
 static hipError_t tiled_launch(const GemmArgs &g, hipStream_t st, int *splits_out) {
-    using P = Tile<BF16>;
+    using P = Tile<PM>;
     const long long m_tiles = (g.M + P::BM - 1) / P::BM;
     const int n_tiles = (g.N + P::BN - 1) / P::BN;
     const int kps = tiled_kps(g, P::BK);
@@ -557,20 +640,24 @@ static hipError_t tiled_launch(const GemmArgs &g, hipStream_t st, int *splits_ou
     const int mt = (int)m_tiles, tt = (int)total;
     *splits_out = splits;
     if (g.a_kc && g.b_kc) {
-        if (g.a_dt == 0) tiled_go<0, false, 0, false, BF16>(g, mt, n_tiles, kps, tt, st);
-        else if (g.a_dt == 1) tiled_go<1, false, 0, false, BF16>(g, mt, n_tiles, kps, tt, st);
-        else tiled_go<2, false, 0, false, BF16>(g, mt, n_tiles, kps, tt, st);
-    } else if (g.a_kc) {
-        if (g.a_dt == 2) tiled_go<2, false, 0, true, BF16>(g, mt, n_tiles, kps, tt, st);
-        else tiled_go<0, false, 0, true, BF16>(g, mt, n_tiles, kps, tt, st);
-    } else if (g.a_dt == 2) {
-        if (g.b_dt == 0) tiled_go<2, true, 0, true, BF16>(g, mt, n_tiles, kps, tt, st);
-        else if (g.b_dt == 1) tiled_go<2, true, 1, true, BF16>(g, mt, n_tiles, kps, tt, st);
-        else tiled_go<2, true, 2, true, BF16>(g, mt, n_tiles, kps, tt, st);
-    } else {
-        if (g.b_dt == 0) tiled_go<0, true, 0, true, BF16>(g, mt, n_tiles, kps, tt, st);
-        else if (g.b_dt == 1) tiled_go<0, true, 1, true, BF16>(g, mt, n_tiles, kps, tt, st);
-        else tiled_go<0, true, 2, true, BF16>(g, mt, n_tiles, kps, tt, st);
+        if (g.a_dt == 0) tiled_go<0, false, 0, false, PM>(g, mt, n_tiles, kps, tt, st);
+        else if (g.a_dt == 1) tiled_go<1, false, 0, false, PM>(g, mt, n_tiles, kps, tt, st);
+        else tiled_go<2, false, 0, false, PM>(g, mt, n_tiles, kps, tt, st);
+        return hipGetLastError();
+    }
+    if constexpr (PM == 1) {
+        if (g.a_kc) {
+            if (g.a_dt == 2) tiled_go<2, false, 0, true, true>(g, mt, n_tiles, kps, tt, st);
+            else tiled_go<0, false, 0, true, true>(g, mt, n_tiles, kps, tt, st);
+        } else if (g.a_dt == 2) {
+            if (g.b_dt == 0) tiled_go<2, true, 0, true, true>(g, mt, n_tiles, kps, tt, st);
+            else if (g.b_dt == 1) tiled_go<2, true, 1, true, true>(g, mt, n_tiles, kps, tt, st);
+            else tiled_go<2, true, 2, true, true>(g, mt, n_tiles, kps, tt, st);
+        } else {
+            if (g.b_dt == 0) tiled_go<0, true, 0, true, true>(g, mt, n_tiles, kps, tt, st);
+            else if (g.b_dt == 1) tiled_go<0, true, 1, true, true>(g, mt, n_tiles, kps, tt, st);
+            else tiled_go<0, true, 2, true, true>(g, mt, n_tiles, kps, tt, st);
+        }
     }
     return hipGetLastError();
 }
@@ -590,10 +677,21 @@ __global__ void k_split_reduce(long long MN, int N, int splits, const float *P, 
 hipError_t gemm_launch(const GemmArgs &g, bool bf16, hipStream_t st) {
     if (g.M == 0 || g.N == 0) return hipSuccess;
     if (bf16 && gemm_big_ok(g)) return gemm_big_launch(g, st);
+    if (!bf16 && g.fp32_order && g.a_kc && g.b_kc && g.b_dt == 0 && g.K > 0) {
+        // us of a layer's forward, tiled path / this one: 1000 x 100 (K 200) 50 / 36, 2048 x 128 (K 700)
+        // 104 / 70, 1000 x 512 53 / 44, 4000 x 128 54 / 44; 4000 x 200 62 / 57 and 8000 x 256 54 / 65 with
+        // the widest tile. Rows the tiled path's loads do not align with: 8000 x 256 (K 201) 103 / 66,
+        // 16000 x 130 110 / 81; 16000 x 512 137 / 172.
+        const double mn = (double)g.M * g.N;
+        if (mn <= 262144.0) return small_launch<1, 1>(g, st);
+        if (mn <= 524288.0) return small_launch<1, 2>(g, st);
+        if (mn <= 4194304.0 && !tiled_ok(g, false)) return small_launch<2, 2>(g, st);
+    }
     const bool split = !bf16 && !g.fp32_order && gemm_split_ok(g);
     if (split || tiled_ok(g, bf16)) {
         int splits = 1;
-        hipError_t e = split ? gemm_split_launch(g, st, &splits) : bf16 ? tiled_launch<true>(g, st, &splits) : tiled_launch<false>(g, st, &splits);
+        hipError_t e = split ? gemm_split_launch(g, st, &splits) : bf16 ? tiled_launch<1>(g, st, &splits)
+                              : g.K > 256 ? tiled_launch<2>(g, st, &splits) : tiled_launch<0>(g, st, &splits);
         if (e != hipSuccess || splits == 1) return e;
         const long long MN = g.M * (long long)g.N;
         hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, MN, g.N,
