@@ -1,7 +1,7 @@
 // Leaky non-spiking readout (paper supplementary, "Readout neurons"):
 //   I_r = W_r S,  V_r[t] = beta_r V_r[t-1] + (1 - beta_r) I_r[t],  o = sum_t V_r[t],
 // beta_r = exp(-DT / tau_r). The projection runs on the MFMA GEMM; the
-// integration runs in FP64, each (batch, readout neuron) row on 16 threads that take
+// integration runs in FP64, each (batch, readout neuron) row on 32 to 64 threads that take
 // a chunk of time each and join their carries through LDS.
 // Workspace layout (kept by the caller from forward to backward):
 //   I_r [B*T][C] f32 | V_r [B*T][C] f32 | gI_r [B*T][C] f32 | part [B][C] f64 | GEMM split scratch
@@ -44,108 +44,95 @@ RoWs ro_ws(void *ws, int B, int T, int C) {
 // true carry-in,
 //   V_in(k) = sum over k' < k of beta^(Lc (k - 1 - k')) e(k')   (Horner over k'),
 // and reruns its chunk from it, writing V_r and summing it; the chunk sums are added
-// in chunk order. Loads go 32 steps at a time. The backward is the same with the
-// reverse recurrence (its local pass needs no loads) and the carry from the chunks
-// after. Every chunk before the last non-empty one is full, so beta^Lc is the only
-// decay across chunks.
-constexpr int RK = 16;   // chunks a row
-constexpr int RU = 32;   // steps whose loads are issued together
-constexpr int RCG = 32;  // classes a workgroup at most (512 threads: no register spills)
+// in chunk order. Loads go RU steps at a time, and a chunk of at most RU steps stays in
+// registers between the runs. The backward is the same with the reverse recurrence (its
+// local value is a geometric sum) and the carry from the chunks after. Every chunk before
+// the last non-empty one is full, so beta^Lc is the only decay across chunks.
+//
+// What bounds it: latency, a row's chunks on one CU. As many chunks as 1024 threads allow,
+// up to 64, against 16 (with a second local run in the backward): 32 x 20 x 1000 the forward call
+// 72 -> 50 us, the backward call 134 -> 101 us; 32 x 20 x 4000 173 -> 87 and 422 -> 261 us.
+constexpr int RKM = 64;  // chunks a row at most
+constexpr int RU = 24;   // steps whose loads are issued together (128 registers a thread)
+constexpr int RUB = 12;  // in the backward, which reads two rows
+constexpr int RCG = 32;  // classes a workgroup at most
+constexpr int RTH = 1024;
 
-// Run v <- beta v + omb I[t] over t in [t0, t1) from v; with STORE, write V_r and sum v.
+int ro_chunks(int cg) { return RTH / cg < RKM ? RTH / cg : RKM; }
+
+__device__ __forceinline__ void load_fwd(float (&x)[RU], const float *__restrict__ ir, int C, int t0, int t1) {
+#pragma unroll
+    for (int u = 0; u < RU; u++) x[u] = t0 + u < t1 ? ir[(size_t)(t0 + u) * C] : 0.0f;
+}
+
+// Run v <- beta v + omb I[t] over the up to RU steps from t0, I in x; with STORE, write V_r and sum v.
 template <bool STORE>
-__device__ __forceinline__ double run_fwd(const float *__restrict__ ir, float *__restrict__ vr, int C, int t0,
-                                          int t1, double beta, double omb, double v, double &sum) {
-    for (int tb = t0; tb < t1; tb += RU) {
-        float x[RU];
+__device__ __forceinline__ double run_fwd(const float (&x)[RU], float *__restrict__ vr, int C, int t0, int t1,
+                                          double beta, double omb, double v, double &sum) {
 #pragma unroll
-        for (int u = 0; u < RU; u++) x[u] = tb + u < t1 ? ir[(size_t)(tb + u) * C] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < RU; u++)
-            if (tb + u < t1) {
-                v = fma(beta, v, omb * (double)x[u]);
-                if constexpr (STORE) {
-                    vr[(size_t)(tb + u) * C] = (float)v;
-                    sum += v;
-                }
+    for (int u = 0; u < RU; u++)
+        if (t0 + u < t1) {
+            v = fma(beta, v, omb * (double)x[u]);
+            if constexpr (STORE) {
+                vr[(size_t)(t0 + u) * C] = (float)v;
+                sum += v;
             }
-    }
+        }
     return v;
 }
 
-__global__ __launch_bounds__(RK * RCG) void k_readout_fwd(int B, int T, int C, double dt,
-                                                          const float *__restrict__ tau_r,
-                                                          const float *__restrict__ Ir, float *__restrict__ Vr,
-                                                          float *__restrict__ o) {
-    __shared__ double sh[RK][RCG];
-    const int CG = blockDim.x / RK;
+__global__ __launch_bounds__(RTH) void k_readout_fwd(int B, int T, int C, int CG, double dt,
+                                                     const float *__restrict__ tau_r, const float *__restrict__ Ir,
+                                                     float *__restrict__ Vr, float *__restrict__ o) {
+    __shared__ double sh[RTH];
+    const int RK = blockDim.x / CG;
     const int k = threadIdx.x / CG, cl = threadIdx.x - k * CG;
     const int b = blockIdx.x, c = blockIdx.y * CG + cl;
     const bool ok = c < C;
     const double lb = -dt / (double)tau_r[ok ? c : 0];
     const double beta = exp(lb), omb = -expm1(lb);
     const int Lc = (T + RK - 1) / RK;
-    const int t0 = min(T, k * Lc), t1 = min(T, t0 + Lc);
-    const float *ir = Ir + (size_t)b * T * C + c;
-    float *vr = Vr + (size_t)b * T * C + c;
-    double unused = 0.0;
-    sh[k][cl] = ok ? run_fwd<false>(ir, vr, C, t0, t1, beta, omb, 0.0, unused) : 0.0;
+    const int t0 = min(T, k * Lc), t1 = ok ? min(T, t0 + Lc) : t0;
+    const float *ir = Ir + (size_t)b * T * C + (ok ? c : 0);
+    float *vr = Vr + (size_t)b * T * C + (ok ? c : 0);
+    float x[RU];
+    double unused = 0.0, e = 0.0;
+    for (int tb = t0; tb < t1; tb += RU) {
+        load_fwd(x, ir, C, tb, t1);
+        e = run_fwd<false>(x, vr, C, tb, t1, beta, omb, e, unused);
+    }
+    sh[threadIdx.x] = e;
     __syncthreads();
     const double dk = exp(lb * (double)Lc);
-    double vin = 0.0;
-    for (int kk = 0; kk < k; kk++) vin = fma(dk, vin, sh[kk][cl]);
+    double v = 0.0;
+    for (int kk = 0; kk < k; kk++) v = fma(dk, v, sh[kk * CG + cl]);
     double sum = 0.0;
-    if (ok) run_fwd<true>(ir, vr, C, t0, t1, beta, omb, vin, sum);
+    if (Lc <= RU) {   // uniform
+        run_fwd<true>(x, vr, C, t0, t1, beta, omb, v, sum);
+    } else {
+        for (int tb = t0; tb < t1; tb += RU) {
+            load_fwd(x, ir, C, tb, t1);
+            v = run_fwd<true>(x, vr, C, tb, t1, beta, omb, v, sum);
+        }
+    }
     __syncthreads();
-    sh[k][cl] = sum;
+    sh[threadIdx.x] = sum;
     __syncthreads();
     if (ok && k == 0) {
         double tot = 0.0;
-        for (int kk = 0; kk < RK; kk++) tot += sh[kk][cl];
+        for (int kk = 0; kk < RK; kk++) tot += sh[kk * CG + cl];
         o[(size_t)b * C + c] = (float)tot;
     }
 }
 
-// Run lam <- g + beta lam over t = t1 - 1 down to t0 from lam; with ACC, write gI_r
-// and accumulate d/dbeta (V_r[t - 1] - I_r[t]) lam.
-template <bool ACC>
-__device__ __forceinline__ double run_bwd(const float *__restrict__ ir, const float *__restrict__ vr,
-                                          float *__restrict__ gi, int C, int t0, int t1, double beta, double omb,
-                                          double g, double lam, double &gb) {
-    for (int tb = t1 - 1; tb >= t0; tb -= RU) {
-        float xi[RU], xv[RU];
-        if constexpr (ACC) {
-#pragma unroll
-            for (int u = 0; u < RU; u++) {
-                const int t = tb - u;
-                xi[u] = t >= t0 ? ir[(size_t)t * C] : 0.0f;
-                xv[u] = (t >= t0 && t > 0) ? vr[(size_t)(t - 1) * C] : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < RU; u++) {
-            const int t = tb - u;
-            if (t >= t0) {
-                lam = fma(beta, lam, g);
-                if constexpr (ACC) {
-                    gi[(size_t)t * C] = (float)(omb * lam);
-                    gb = fma((double)xv[u] - (double)xi[u], lam, gb);
-                }
-            }
-        }
-    }
-    return lam;
-}
-
 // reverse recurrence lam[t] = go + beta lam[t+1]; gI_r[t] = (1 - beta) lam[t];
 // d/dbeta = sum_t (V_r[t-1] - I_r[t]) lam[t]
-__global__ __launch_bounds__(RK * RCG) void k_readout_bwd(int B, int T, int C, double dt,
-                                                          const float *__restrict__ tau_r,
-                                                          const float *__restrict__ Ir, const float *__restrict__ Vr,
-                                                          const float *__restrict__ go, float *__restrict__ gIr,
-                                                          double *__restrict__ part) {
-    __shared__ double sh[RK][RCG];
-    const int CG = blockDim.x / RK;
+__global__ __launch_bounds__(RTH) void k_readout_bwd(int B, int T, int C, int CG, double dt,
+                                                     const float *__restrict__ tau_r, const float *__restrict__ Ir,
+                                                     const float *__restrict__ Vr, const float *__restrict__ go,
+                                                     float *__restrict__ gIr, double *__restrict__ part) {
+    __shared__ double sh[RTH];
+    const int RK = blockDim.x / CG;
     const int k = threadIdx.x / CG, cl = threadIdx.x - k * CG;
     const int b = blockIdx.x, c = blockIdx.y * CG + cl;
     const bool ok = c < C;
@@ -153,26 +140,37 @@ __global__ __launch_bounds__(RK * RCG) void k_readout_bwd(int B, int T, int C, d
     const double beta = exp(lb), omb = -expm1(lb);
     const double g = ok ? (double)go[(size_t)b * C + c] : 0.0;
     const int Lc = (T + RK - 1) / RK;
-    const int t0 = min(T, k * Lc), t1 = min(T, t0 + Lc);
-    const size_t base = (size_t)b * T * C + c;
+    const int t0 = min(T, k * Lc), t1 = ok ? min(T, t0 + Lc) : t0;
+    const size_t base = (size_t)b * T * C + (ok ? c : 0);
     const float *ir = Ir + base, *vr = Vr + base;
     float *gi = gIr + base;
-    double unused = 0.0;
-    // lambda at this chunk's first step from a zero carry at its end
-    sh[k][cl] = ok ? run_bwd<false>(ir, vr, gi, C, t0, t1, beta, omb, g, 0.0, unused) : 0.0;
-    __syncthreads();
-    // the carry at this chunk's end: the later chunks' values, Horner from the last
-    const double dk = exp(lb * (double)Lc);
-    double lin = 0.0;
-    for (int kk = RK - 1; kk > k; kk--) lin = fma(dk, lin, sh[kk][cl]);
+    // the carry at this chunk's end: lambda at step t1 from the T - t1 steps of the later
+    // chunks, g (1 + beta + ... + beta^(T - t1 - 1))
+    double lam = omb > 0.0 ? g * (-expm1(lb * (double)(T - t1)) / omb) : g * (double)(T - t1);
     double gb = 0.0;
-    if (ok) run_bwd<true>(ir, vr, gi, C, t0, t1, beta, omb, g, lin, gb);
-    __syncthreads();
-    sh[k][cl] = gb;
+    for (int tb = t1 - 1; tb >= t0; tb -= RUB) {
+        float xi[RUB], xv[RUB];
+#pragma unroll
+        for (int u = 0; u < RUB; u++) {
+            const int t = tb - u;
+            xi[u] = t >= t0 ? ir[(size_t)t * C] : 0.0f;
+            xv[u] = (t >= t0 && t > 0) ? vr[(size_t)(t - 1) * C] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < RUB; u++) {
+            const int t = tb - u;
+            if (t >= t0) {
+                lam = fma(beta, lam, g);
+                gi[(size_t)t * C] = (float)(omb * lam);
+                gb = fma((double)xv[u] - (double)xi[u], lam, gb);
+            }
+        }
+    }
+    sh[threadIdx.x] = gb;
     __syncthreads();
     if (ok && k == 0) {
         double tot = 0.0;
-        for (int kk = 0; kk < RK; kk++) tot += sh[kk][cl];
+        for (int kk = 0; kk < RK; kk++) tot += sh[kk * CG + cl];
         part[(size_t)b * C + c] = tot;
     }
 }
@@ -181,7 +179,8 @@ __global__ void k_readout_tau(int B, int C, double dt, const float *tau_r, const
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
     double s = 0.0;
-    for (int b = 0; b < B; b++) s += part[(size_t)b * C + c];
+#pragma unroll 16
+    for (int b = 0; b < B; b++) s += part[(size_t)b * C + c];   // (loads in flight, added in order)
     const double tau = tau_r[c];
     g_tau[c] = (float)(s * exp(-dt / tau) * dt / (tau * tau));
 }
@@ -235,8 +234,8 @@ int alif_readout_forward(int32_t B, int32_t T, int32_t n_hidden, int32_t C, doub
     if (e != hipSuccess) return alif::set_error(ALIF_EHIP, hipGetErrorString(e));
     if (B == 0) return ALIF_OK;
     const int cg = C < RCG ? C : RCG;
-    hipLaunchKernelGGL(k_readout_fwd, dim3((unsigned)B, (unsigned)((C + cg - 1) / cg)), dim3(RK * cg), 0, st, B, T,
-                       C, dt_ms, tau_r, w.Ir, w.Vr, o);
+    hipLaunchKernelGGL(k_readout_fwd, dim3((unsigned)B, (unsigned)((C + cg - 1) / cg)),
+                       dim3(ro_chunks(cg) * cg), 0, st, B, T, C, cg, dt_ms, tau_r, w.Ir, w.Vr, o);
     e = hipGetLastError();
     if (e != hipSuccess) return alif::set_error(ALIF_EHIP, hipGetErrorString(e));
     return ALIF_OK;
@@ -256,8 +255,8 @@ int alif_readout_backward(int32_t B, int32_t T, int32_t n_hidden, int32_t C, dou
     RoWs w = ro_ws(workspace, B, T, C);
     if (B > 0) {
         const int cg = C < RCG ? C : RCG;
-        hipLaunchKernelGGL(k_readout_bwd, dim3((unsigned)B, (unsigned)((C + cg - 1) / cg)), dim3(RK * cg), 0, st, B,
-                           T, C, dt_ms, tau_r, w.Ir, w.Vr, go, w.gIr, w.part);
+        hipLaunchKernelGGL(k_readout_bwd, dim3((unsigned)B, (unsigned)((C + cg - 1) / cg)),
+                           dim3(ro_chunks(cg) * cg), 0, st, B, T, C, cg, dt_ms, tau_r, w.Ir, w.Vr, go, w.gIr, w.part);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return alif::set_error(ALIF_EHIP, hipGetErrorString(e));
     }
