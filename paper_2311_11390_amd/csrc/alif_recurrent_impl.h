@@ -23,10 +23,13 @@
 // over the active presynaptic neurons in increasing index, added once to the
 // feed-forward current: the order of the per-block recurrent-current kernel.
 //
-// Two kernels run it. k_recurrent_fused does all of it and writes every output
-// itself; it serves the calls that want V and theta traces, which only this loop has.
-// k_recurrent_slice leaves the two streams of the size of the layer (the whole current
-// and the spikes) to other workgroups: see there.
+// Two kernels run it. k_recurrent_fused does all of it and writes every output itself:
+// for the calls that want V and theta traces, which only this loop has, and for short
+// runs. Its stores cost it half of its time (a workgroup issues them for every step of
+// every neuron while one block runs), so with CHUNKED (N a multiple of 16 and room in
+// LDS) they go out as 16-byte chunks: the block's current through a wave-private LDS tile,
+// and the spikes packed from one ballot per step. k_recurrent_slice leaves these two
+// streams to other workgroups: see there.
 #pragma once
 #include "alif_blocks_impl.h"
 
@@ -38,14 +41,24 @@ __host__ __device__ constexpr size_t rec_smem_fixed(int TR) {
     return (size_t)64 * NG * TR * sizeof(double) + (size_t)3 * SEG * 64 * NG * 4;
 }
 
-// Non-temporal (streamed) access for the feed-forward current, which so passes through
-// L2 without evicting the W_rec^T rows the gather reads every block.
+// LDS of the CHUNKED staging tile: [waves][L][64] floats after the 16-byte aligned fixed part
+template <int SEG, int L, int NG>
+__host__ __device__ constexpr size_t rec_stage_bytes() {
+    return (size_t)NG * SEG * L * 64 * 4;
+}
+__host__ __device__ constexpr size_t rec_stage_offset(size_t fixed_and_ring) { return (fixed_and_ring + 15) & ~(size_t)15; }
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// Non-temporal (streamed) access for the feed-forward current read once and the
+// whole current and spikes written once, so that they pass through L2 without
+// evicting the W_rec^T rows the gather reads every block (about 1% of the loop).
 constexpr int REC_NT = 2;
 __device__ __forceinline__ float ld_f32_nt(rsrc_t r, uint32_t byte_off) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, REC_NT));
 }
 
-template <int SEG, int L, bool EVEN, int NG>
+template <int SEG, int L, bool EVEN, int NG, bool TRACES, bool CHUNKED>
 __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_fused(RecArgs a) {
     constexpr int NWG = 64 * NG;
     constexpr int DEPTH = 2;
@@ -56,6 +69,10 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_fused(RecArgs a) {
     float *exX = reinterpret_cast<float *>(smem + (size_t)NWG * TR * sizeof(double));
     int *exC = reinterpret_cast<int *>(exX + SEG * NWG);
     uint8_t *ring = reinterpret_cast<uint8_t *>(exC + 2 * SEG * NWG);
+    // this wave's staging tile [L][64] (CHUNKED)
+    float *stg = reinterpret_cast<float *>(
+                     smem + rec_stage_offset(rec_smem_fixed<SEG, NG>(TR) + (size_t)R * NWG)) +
+                 (size_t)(threadIdx.x >> 6) * L * 64;
 
     const int b = blockIdx.x;
     build_p_tables<SEG, L, NWG>(pd_tab, nullptr, 0, N, TR, a.dt, a.tau_a);
@@ -159,7 +176,8 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_fused(RecArgs a) {
 #pragma unroll
         for (int k = 0; k < L; k++) {
             x[k] = (hit >> k) & 1u ? bi[k] + acc[k] : bi[k];   // uniform: a row with a recurrent term
-            st_f32(rI, c.off(k, bo), x[k]);
+            if constexpr (CHUNKED) stg[k * 64 + lane] = x[k];
+            else st_f32(rI, c.off(k, bo), x[k]);
         }
         const float cv = (float)v0d, ca = (float)a0d;
         const int mpre = cts > 0 ? cts - 1 : 0;
@@ -195,12 +213,14 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_fused(RecArgs a) {
         for (int k = 0; k < L; k++) {
             const int t = c.t0 + k + 1;
             const uint32_t o4 = c.off(k, bo);
-            st_spike(rS, a.spike_dtype, o4 >> spk_shift | (o4 & ALIF_OOB), t == ts);
-            const bool after = t > ts;
-            st_f32(rV, o4, after ? 0.0f : vt[k]);
-            // p^(t - 1 - t_s) when after (clamped into the row for the steps that are not)
-            const float pa = (float)pd_tab[pdrow + min(TR - 1, max(0, t - 1 - ts))];
-            st_f32(rT, o4, after ? fmaf(c.dd, pa, th[k]) : th[k]);
+            if constexpr (!CHUNKED) st_spike(rS, a.spike_dtype, o4 >> spk_shift | (o4 & ALIF_OOB), t == ts);
+            if constexpr (TRACES) {
+                const bool after = t > ts;
+                st_f32(rV, o4, after ? 0.0f : vt[k]);
+                // p^(t - 1 - t_s) when after (clamped into the row for the steps that are not)
+                const float pa = (float)pd_tab[pdrow + min(TR - 1, max(0, t - 1 - ts))];
+                st_f32(rT, o4, after ? fmaf(c.dd, pa, th[k]) : th[k]);
+            }
         }
         const bool spk = ts <= TR;
         const double e1 = cts == TR ? c.pTm1 : 0.0;
@@ -210,6 +230,55 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_fused(RecArgs a) {
         a0d = fma(c.pT, a0d, extra);
         cts = spk ? ts : 0;
         if (R > 0 && c.w == 0) ring[(nb % R) * NWG + c.nl] = (uint8_t)(spk ? ts : 0);
+        if constexpr (CHUNKED) {
+            const int nw0 = c.n - lane;                     // first neuron of this wave's group
+            const int row0 = nb * TR + c.t0;                // first step of this wave's segment
+            // spikes: a ballot per step; 16-byte chunks of NPC = 16 / SB neurons, 4 SB per step row
+            uint64_t m[L];
+#pragma unroll
+            for (int k = 0; k < L; k++) m[k] = __ballot(c.t0 + k + 1 == ts);
+            const int CPR = 4 * SB, NPC = 16 / SB;
+            // a fixed number of store instructions (the f32 count; chunks past CPR L are dropped)
+#pragma unroll
+            for (int ci0 = 0; ci0 < 16 * L; ci0 += 64) {
+                const int ci = ci0 + lane, k = ci / CPR, q = ci - k * CPR;
+                uint64_t mk = 0;
+#pragma unroll
+                for (int kk = 0; kk < L; kk++) mk = k == kk ? m[kk] : mk;
+                const uint32_t bits = (uint32_t)(mk >> (q * NPC));
+                u32x4_t v;
+                if (SB == 1) {   // bytes 0 / 1: spread each nibble to four bytes
+                    v.x = ((bits & 15u) * 0x204081u) & 0x01010101u;
+                    v.y = (((bits >> 4) & 15u) * 0x204081u) & 0x01010101u;
+                    v.z = (((bits >> 8) & 15u) * 0x204081u) & 0x01010101u;
+                    v.w = (((bits >> 12) & 15u) * 0x204081u) & 0x01010101u;
+                } else if (SB == 2) {   // bfloat16 1.0 = 0x3F80
+                    v.x = (bits & 1u ? 0x3F80u : 0u) | (bits & 2u ? 0x3F800000u : 0u);
+                    v.y = (bits & 4u ? 0x3F80u : 0u) | (bits & 8u ? 0x3F800000u : 0u);
+                    v.z = (bits & 16u ? 0x3F80u : 0u) | (bits & 32u ? 0x3F800000u : 0u);
+                    v.w = (bits & 64u ? 0x3F80u : 0u) | (bits & 128u ? 0x3F800000u : 0u);
+                } else {
+                    v.x = bits & 1u ? 0x3F800000u : 0u;
+                    v.y = bits & 2u ? 0x3F800000u : 0u;
+                    v.z = bits & 4u ? 0x3F800000u : 0u;
+                    v.w = bits & 8u ? 0x3F800000u : 0u;
+                }
+                const bool ok = ci < CPR * L && k < c.len && nw0 + q * NPC < N;
+                const uint32_t off = ok ? (uint32_t)(((size_t)(row0 + k) * N + nw0 + q * NPC) * SB) : ALIF_OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(v, rS, off, 0, REC_NT);
+            }
+            // the whole current of the block from the staging tile: 16 chunks of 4 neurons per step row
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int ci0 = 0; ci0 < 16 * L; ci0 += 64) {
+                const int ci = ci0 + lane, k = ci >> 4, q = ci & 15;
+                const bool ok = ci < 16 * L && k < c.len && nw0 + 4 * q < N;
+                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(&stg[(ok ? k : 0) * 64 + 4 * q]);
+                const uint32_t off = ok ? (uint32_t)(((size_t)(row0 + k) * N + nw0 + 4 * q) * 4) : ALIF_OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(v, rI, off, 0, REC_NT);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
         const uint32_t nxt = (uint32_t)min((size_t)(nb + DEPTH) * blk4, TN * 4);
 #pragma unroll
         for (int k = 0; k < L; k++) bi[k] = ld_f32_nt(rIn, c.off(k, nxt));
@@ -274,9 +343,14 @@ constexpr size_t rec_slice_smem(int R) {
 // lane and as many rows side by side as fit 64 lanes. It streams every row through (the
 // current only where it does not lie in place already), except the current of the few rows
 // that events land in, which the chain has marked (hits); these follow.
+template <int VEC, typename V>
+__device__ __forceinline__ void rec_put(V w, V *p) {
+    if constexpr (VEC == 4) __builtin_nontemporal_store(w, p);
+    else *p = w;
+}
 template <int SEG, int L, int VEC>
 __device__ __forceinline__ void rec_expand(const RecArgs &a, int wave, int waves) {
-    constexpr int G = L >= 16 ? 1 : (16 + L - 1) / L, U = 4;
+    constexpr int G = L >= 16 ? 1 : (16 + L - 1) / L, U = VEC == 4 ? 4 : 8;
     const int lane = threadIdx.x & 63;
     const int N = a.N, TR = a.TR, T = a.T, D = a.D;
     int tpr = 1;
@@ -322,22 +396,22 @@ __device__ __forceinline__ void rec_expand(const RecArgs &a, int wave, int waves
                     const int q = q0 + u * rpw + sub, nt = blk0 + q / L, k = step[u];
                     const size_t o = b * TN + (size_t)(nt * TR + k) * N + n;
                     if (!in_place && !(hw[u] >> (k - seg * L) & 1u))
-                        __builtin_nontemporal_store(x[u], reinterpret_cast<vecf *>(a.I + o));
+                        rec_put<VEC>(x[u], reinterpret_cast<vecf *>(a.I + o));
                     if (a.spike_dtype == 0) {
                         vec1 w;
 #pragma unroll
                         for (int v = 0; v < VEC; v++) w[v] = own[u][v] == k + 1 ? 1 : 0;
-                        __builtin_nontemporal_store(w, reinterpret_cast<vec1 *>(static_cast<uint8_t *>(a.spikes) + o));
+                        rec_put<VEC>(w, reinterpret_cast<vec1 *>(static_cast<uint8_t *>(a.spikes) + o));
                     } else if (a.spike_dtype == 1) {
                         vec2 w;
 #pragma unroll
                         for (int v = 0; v < VEC; v++) w[v] = own[u][v] == k + 1 ? 0x3F80 : 0;
-                        __builtin_nontemporal_store(w, reinterpret_cast<vec2 *>(static_cast<uint16_t *>(a.spikes) + o));
+                        rec_put<VEC>(w, reinterpret_cast<vec2 *>(static_cast<uint16_t *>(a.spikes) + o));
                     } else {
                         vecf w;
 #pragma unroll
                         for (int v = 0; v < VEC; v++) w[v] = own[u][v] == k + 1 ? 1.0f : 0.0f;
-                        __builtin_nontemporal_store(w, reinterpret_cast<vecf *>(static_cast<float *>(a.spikes) + o));
+                        rec_put<VEC>(w, reinterpret_cast<vecf *>(static_cast<float *>(a.spikes) + o));
                     }
                 }
             }
@@ -579,6 +653,16 @@ inline int rec_slices(double bytes, int NB) {
     return s < 1 ? 1 : (s > 8 ? 8 : s);
 }
 
+// Which runs go in slices. They save a chain about 0.1 ns a step and neuron and cost the run
+// some 50 us (two more launches, the last slice's expansion): forward, us, one launch / slices:
+// 64 x 1000 x 256 182 / 200, 64 x 2500 x 128 284 / 293, 64 x 4000 x 128 442 / 440, 32 x 4000 x 256
+// 495 / 413, 64 x 15000 x 64 816 / 558. Rows that do not align four neurons expand at a quarter of
+// the rate, which many of them beside the chain do not hide: 32 x 2000 x 255 264 / 288, 32 x 8000 x 255
+// 974 / 802, 64 x 8000 x 201 955 / 1161.
+inline bool rec_sliced(int B, int T, int N, bool vec4) {
+    return (long long)T * N >= (vec4 ? 500000 : 800000) && (vec4 || (long long)B * N <= 8192);
+}
+
 // W_rec transposed, and pd[n][k] = p^k in FP64, k < T_R: the values of the block forward's table
 static __global__ void k_rec_setup(int N, int TR, double dt, const float *tau_a, const float *Wrec, float *WrecT,
                                    double *pd) {
@@ -595,17 +679,27 @@ hipError_t recurrent_fused_launch(RecArgs a, hipStream_t st) {
     const int setup = a.N * (a.N > a.TR ? a.N : a.TR);
     hipLaunchKernelGGL(k_rec_setup, dim3((setup + 255) / 256), dim3(256), 0, st, a.N, a.TR, a.dt, a.tau_a, a.Wrec, a.WrecT,
                        a.pd);
-    if (a.V || a.TH) {
-        const size_t sm = rec_smem_fixed<SEG, NG>(a.TR) + (size_t)a.ring * 64 * NG;
-        if (even) hipLaunchKernelGGL((k_recurrent_fused<SEG, L, true, NG>), dim3(a.B), blk, sm, st, a);
-        else hipLaunchKernelGGL((k_recurrent_fused<SEG, L, false, NG>), dim3(a.B), blk, sm, st, a);
+    const int sb = a.spike_dtype == 0 ? 1 : (a.spike_dtype == 1 ? 2 : 4);
+    a.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.I) | reinterpret_cast<uintptr_t>(a.I_ff)) & 15) == 0 &&
+             (reinterpret_cast<uintptr_t>(a.spikes) & (4 * sb - 1)) == 0;
+    const bool tr = a.V || a.TH;
+    if (tr || !rec_sliced(a.B, a.T, a.N, a.vec4)) {
+        const size_t base = rec_smem_fixed<SEG, NG>(a.TR) + (size_t)a.ring * 64 * NG;
+        const size_t smc = rec_stage_offset(base) + rec_stage_bytes<SEG, L, NG>();
+        // chunked stores: whole 16-neuron chunks in every row and room for the staging tile
+        const bool chunked = !tr && a.N % 16 == 0 && smc <= (size_t)160 * 1024;
+        const size_t smf = chunked ? smc : base;
+#define ALIF_LR(EV, TRC, CH) hipLaunchKernelGGL((k_recurrent_fused<SEG, L, EV, NG, TRC, CH>), dim3(a.B), blk, smf, st, a)
+        if (even) {
+            if (tr) ALIF_LR(true, true, false); else if (chunked) ALIF_LR(true, false, true); else ALIF_LR(true, false, false);
+        } else {
+            if (tr) ALIF_LR(false, true, false); else if (chunked) ALIF_LR(false, false, true); else ALIF_LR(false, false, false);
+        }
+#undef ALIF_LR
         return hipGetLastError();
     }
     const size_t sm = rec_slice_smem<SEG, L, NG>(a.ring);
     constexpr int WV = NG * SEG;
-    const int sb = a.spike_dtype == 0 ? 1 : (a.spike_dtype == 1 ? 2 : 4);
-    a.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.I) | reinterpret_cast<uintptr_t>(a.I_ff)) & 15) == 0 &&
-             (reinterpret_cast<uintptr_t>(a.spikes) & (4 * sb - 1)) == 0;
     const int slices = rec_slices((double)a.B * a.T * a.N * (8 + sb), a.NB), per = (a.NB + slices - 1) / slices;
     for (int s = 0; s <= slices; s++) {
         a.xb0 = a.nb0;

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("TR,delay,T,N,sdt,spikes_in", [
     (10, 0, 6003, 256, 0, False), (10, 37, 6003, 255, 1, False), (40, 0, 6000, 256, 2, False),
-    (2, 5, 6001, 130, 0, True), (40, 80, 6017, 200, 0, True), (47, 50, 6100, 128, 1, False)])
+    (2, 5, 6001, 130, 0, True), (40, 80, 6017, 200, 0, True), (47, 50, 6100, 128, 1, False),
+    (10, 0, 1003, 256, 0, False), (20, 30, 801, 255, 1, False), (40, 0, 900, 128, 2, True)])   # (one launch)
 def test_slices_equal_one_launch(TR, delay, T, N, sdt, spikes_in):
     import torch
 
