@@ -48,16 +48,16 @@ def algorithmic_bytes(TR):
     """Bytes per neuron-step the method must move: forward reads I (4 B) and writes
     the spike (1 B) and, once per T_R-step block, the block's carry-in (V0 and a
     as float, the previous spike step as a byte: 9 B); the backward reads I and
-    dL/dS (4 + 4 B) and the carries. Traces, gradients of I and anything the
+    dL/dS (4 + 4 B) and each block's spike step (1 B). Traces, gradients of I and anything the
     method could avoid are not counted."""
-    return {"fwd": 4.0 + 1.0 + 9.0 / TR, "bwd": 8.0 + 9.0 / TR}
+    return {"fwd": 4.0 + 1.0 + 9.0 / TR, "bwd": 8.0 + 1.0 / TR}
 
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 COUNTERS = os.path.join(HERE, "profiles", "block_fwd_bwd_fine_dt_hbm_counters.md")
 KERNEL_SOURCES = ["alif_blocks.hip", "alif_blocks_impl.h", "alif_blocks_s1.hip", "alif_blocks_s2.hip",
                   "alif_blocks_s4.hip", "alif_blocks_s8.hip", "alif_blocks_s8_long.hip", "alif_blocks_s8_xl.hip",
-                  "alif_common.h", "alif_kernels.h"]
+                  "alif_bwd_stream.hip", "alif_common.h", "alif_kernels.h"]
 
 
 def kernel_sources_digest():

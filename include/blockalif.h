@@ -85,7 +85,8 @@ enum alif_input_kind {
     ALIF_INPUT_SPIKES_F32  = 3  /* x as float 0/1 [B][T][n_in] */
 };
 enum alif_gemm_precision {
-    ALIF_GEMM_FP32 = 0,  /* I~ = b + W x with FP32 MFMA (v_mfma_f32_16x16x4_f32) */
+    ALIF_GEMM_FP32 = 0,  /* FP32 products and sums: a layer's I~ = b + W x by FP32 MFMA over increasing
+                            input index, the other products from exact bfloat16 pieces of each float */
     ALIF_GEMM_BF16 = 1   /* W and x rounded to bfloat16, FP32 accumulation (MFMA) */
 };
 enum alif_spike_dtype { ALIF_SPIKES_U8 = 0, ALIF_SPIKES_BF16 = 1, ALIF_SPIKES_F32 = 2 };
@@ -188,7 +189,7 @@ int alif_decay_tables(const alif_desc *desc, const alif_params *prm,
  *   input   device spikes [B][T][n_in] of desc->input_kind (0/1 values)
  *   W       device float [N][n_in]; bias device float [N] or NULL
  *   current device float [B][T][N] output
- * FP32 precision uses FP32 MFMA; BF16 rounds W to bfloat16 (x is exact) and
+ * FP32 precision multiplies exactly and sums in FP32; BF16 rounds W to bfloat16 (x is exact) and
  * accumulates in FP32.
  */
 int alif_input_current(const alif_desc *desc, const void *input, const float *W,
