@@ -2,8 +2,8 @@
 pass backward in time over the same chunks): dL/dI and the parameter gradients against the
 oracle's sequential adjoint on the teacher-forced forward, to the gradient bar of
 parity.check_grad. T_R on both sides of every grouping, T with a ragged last block, one
-chunk and several, neuron tails, each subset of the incoming gradients (none: zeros), a
-run that starts from a saved state inside a refractory period, dL/dI written over dL/dS."""
+chunk and several, neuron tails, subsets of the incoming gradients (none: zeros), a run
+that starts from a saved state inside a refractory period."""
 import numpy as np
 import pytest
 
