@@ -189,11 +189,10 @@ int set_error(int code, const char *msg) { return fail(code, "%s", msg); }
 // Backward workspace: FP64 partial sums [5][B][N]; for spike input the weight-gradient
 // GEMM's split partials and the event path's count, masks and partials (both are
 // enqueued, one runs); with BF16 GEMMs, W transposed and rounded to bfloat16 once
-// for the input gradient, then the input-current gradient [B][T][N] for a call that
-// passes no grad_current: as bfloat16, or as float behind the chunks' sums where the
-// streaming backward takes the call.
+// for the input gradient, then the input-current gradient as bfloat16 [B][T][N] for
+// a call that passes no grad_current.
 struct BwdWs {
-    size_t part, gemm, wgev, wt, gi16, gi16_end, gi32, gi32_end, total;
+    size_t part, gemm, wgev, wt, gi16, gi16_end, total;
 };
 BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
     BwdWs w;
@@ -206,23 +205,21 @@ BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
     w.total = w.gi16_end = w.gi16 + (bf ? align256((size_t)p.B * p.T * p.N * 2) : 0);
     // the streaming backward keeps its chunks' sums over the regions behind the partial sums:
     // they are joined before anything else is written there
-    w.gi32 = w.gi32_end = 0;
     if (desc->algo == ALIF_ALGO_BLOCKS) {
         const size_t st = bwd_stream_bytes(p.B, p.N, bwd_stream_chunks(p.B, p.T, p.N, p.TR, SIZE_MAX));
         w.total = w.total > st ? w.total : st;
-        if (bf && p.N % 8 == 0 && bwd_stream_gi(p.B, p.T, p.N, p.TR, false, SIZE_MAX)) {
-            w.gi32 = align256(w.gi16 > st ? w.gi16 : st);
-            w.gi32_end = w.gi32 + align256((size_t)p.B * p.T * p.N * 4);
-            w.total = w.total > w.gi32_end ? w.total : w.gi32_end;
-        }
     }
     return w;
 }
 // Whether the streaming backward takes a call (detached block backward): always without an
-// input-current gradient, with a float one by size.
+// input-current gradient, with a float one by size. Under BF16 GEMMs the input-current
+// gradient is the block kernel's: the projections' gradients round it to bfloat16, and the
+// 1e-6 between the two kernels moves enough elements over a rounding boundary to change
+// dW and dx in the fifth digit.
 bool bwd_streams(const alif_desc *desc, const Prob &p, bool grad_current, bool gi16, bool grad_vt, size_t max_bytes) {
     return desc->algo == ALIF_ALGO_BLOCKS && desc->grad_policy != ALIF_GRAD_ATTACHED && !gi16 &&
-           (!grad_current || bwd_stream_gi(p.B, p.T, p.N, p.TR, grad_vt, max_bytes));
+           (!grad_current || (desc->gemm_precision != ALIF_GEMM_BF16 &&
+                              bwd_stream_gi(p.B, p.T, p.N, p.TR, grad_vt, max_bytes)));
 }
 // Whether a backward call keeps the input-current gradient as bfloat16 in its
 // workspace: spike input, BF16 GEMMs, the detached block backward, no gV / gTheta,
@@ -462,14 +459,8 @@ static int backward_impl(const alif_desc *desc, const alif_params *prm, const vo
         return ALIF_OK;
     }
     if (!input || !carries || !workspace) return fail(ALIF_EINVAL, "input, carries and workspace are required");
-    bool gi16 = bwd_gi16(desc, p, grad_current != nullptr, grad_v || grad_theta, grad_W || grad_input);
+    const bool gi16 = bwd_gi16(desc, p, grad_current != nullptr, grad_v || grad_theta, grad_W || grad_input);
     const BwdWs lay = bwd_ws_layout(desc, p);
-    if (gi16 && lay.gi32_end && lay.gi32_end <= max_bytes) {
-        // the float gI the streaming backward fills for a caller's grad_current, in the
-        // workspace: the GEMMs round it to the same bits
-        gi16 = false;
-        grad_current = (float *)((char *)workspace + lay.gi32);
-    }
     if (p.spikes_in) {
         if (!current || !W) return fail(ALIF_EINVAL, "spike input: pass W and the current workspace alif_forward filled");
         if ((grad_W || grad_input) && !grad_current && !gi16)

@@ -1,0 +1,23 @@
+"""The library's own dispatch rules, for tests that have to reach one kernel. They are
+plain host functions of the library (C++, hence the mangled names), so a test that
+names a path fails when a rule moves it to another."""
+import ctypes
+
+from paper_2311_11390_amd import _lib as L
+
+_SIZE_MAX = ctypes.c_size_t(-1).value
+
+
+def streams_dI(B, T, N, TR, gvt=False) -> bool:
+    """Whether the detached backward with a float dL/dI streams over time chunks
+    (``gvt``: with dL/dV or dL/dtheta); else it is the block kernel."""
+    f = getattr(L.load(), "_ZN4alif13bwd_stream_giEiiiibm")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 4 + [ctypes.c_bool, ctypes.c_size_t]
+    return f(B, T, N, TR, gvt, _SIZE_MAX)
+
+
+def stream_chunks(B, T, N, TR) -> int:
+    """Time chunks a row of the streaming backward is cut into."""
+    f = getattr(L.load(), "_ZN4alif17bwd_stream_chunksEiiiim")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_size_t]
+    return f(B, T, N, TR, _SIZE_MAX)
