@@ -167,7 +167,8 @@ int alif_refractory_steps(double dt_ms, double arp_ms);
 int alif_carry_bytes(const alif_desc *desc, size_t *bytes);
 
 /* Bytes of device scratch alif_backward needs (per-(b, neuron) FP64 partial sums, of each
- * time chunk where a call wants no input-current gradient). */
+ * time chunk where a call streams over chunks; for spike input the scratch of the
+ * projections' gradients). */
 int alif_backward_workspace_bytes(const alif_desc *desc, size_t *bytes);
 
 /* ---- compute ----------------------------------------------------------------- */
@@ -329,10 +330,9 @@ int alif_backward(const alif_desc *desc, const alif_params *prm,
  * For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving or training loops, harnesses that forbid hipMalloc): the same
  * backward as alif_backward, same arguments and results, without the workspace
- * argument. Its scratch (the FP64 partial sums, 40 bytes per (b, neuron), and 96 per time
- * chunk where the call is cut into chunks that fit, plus the
- * weight-gradient GEMM's split-K tiles when grad_W is requested for spike input)
- * lives in a static device array of ALIF_NOALLOC_SCRATCH_BYTES inside the library,
+ * argument. Its scratch (the FP64 partial sums, 40 bytes per (b, neuron) or 80 per time
+ * chunk, of which no call takes more than fit, plus the weight-gradient GEMM's split-K
+ * tiles when grad_W is requested for spike input) lives in a static device array of ALIF_NOALLOC_SCRATCH_BYTES inside the library,
  * one per device, held until the process ends. This call allocates nothing: no
  * hipMalloc, hipFree or allocating library routine. A problem whose scratch
  * exceeds the array (the parts of alif_backward_workspace_bytes the call uses:

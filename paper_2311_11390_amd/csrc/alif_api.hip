@@ -203,10 +203,10 @@ BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
     const bool bf = p.spikes_in && desc->gemm_precision == ALIF_GEMM_BF16;
     w.gi16 = w.wt + (bf ? align256(gemm_wbf16_bytes(p.N, p.n_in)) : 0);
     w.total = w.gi16_end = w.gi16 + (bf ? align256((size_t)p.B * p.T * p.N * 2) : 0);
-    // the streaming backward keeps its chunks' sums over the regions behind the partial sums:
-    // they are joined before anything else is written there
+    // the streaming backward keeps its chunks' sums from the start of the scratch on, over the
+    // other regions: they are joined before anything else is written there
     if (desc->algo == ALIF_ALGO_BLOCKS) {
-        const size_t st = bwd_stream_bytes(p.B, p.N, bwd_stream_chunks(p.B, p.T, p.N, p.TR, SIZE_MAX));
+        const size_t st = bwd_stream_bytes(p.B, p.N, bwd_stream_chunks(p.B, p.T, p.N, p.TR));
         w.total = w.total > st ? w.total : st;
     }
     return w;
@@ -216,10 +216,10 @@ BwdWs bwd_ws_layout(const alif_desc *desc, const Prob &p) {
 // gradient is the block kernel's: the projections' gradients round it to bfloat16, and the
 // 1e-6 between the two kernels moves enough elements over a rounding boundary to change
 // dW and dx in the fifth digit.
-bool bwd_streams(const alif_desc *desc, const Prob &p, bool grad_current, bool gi16, bool grad_vt, size_t max_bytes) {
+bool bwd_streams(const alif_desc *desc, const Prob &p, bool grad_current, bool gi16, bool grad_vt) {
     return desc->algo == ALIF_ALGO_BLOCKS && desc->grad_policy != ALIF_GRAD_ATTACHED && !gi16 &&
            (!grad_current || (desc->gemm_precision != ALIF_GEMM_BF16 &&
-                              bwd_stream_gi(p.B, p.T, p.N, p.TR, grad_vt, max_bytes)));
+                              bwd_stream_gi(p.B, p.T, p.N, p.TR, grad_vt)));
 }
 // Whether a backward call keeps the input-current gradient as bfloat16 in its
 // workspace: spike input, BF16 GEMMs, the detached block backward, no gV / gTheta,
@@ -424,15 +424,12 @@ int alif_forward(const alif_desc *desc, const alif_params *prm, const void *inpu
     return ALIF_OK;
 }
 
-}  // extern "C"
-
-// alif_backward with at most max_bytes for the partial sums of the streaming backward.
-static int backward_impl(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
-                         const float *current, const void *carries, const float *grad_spikes,
-                         const float *grad_v, const float *grad_theta, float *grad_current,
-                         float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
-                         float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
-                         void *stream, size_t max_bytes) {
+int alif_backward(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
+                  const float *current, const void *carries, const float *grad_spikes,
+                  const float *grad_v, const float *grad_theta, float *grad_current,
+                  float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
+                  float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
+                  void *stream) {
     Prob p;
     int rc = check_desc(desc, &p);
     if (rc) return rc;
@@ -493,8 +490,8 @@ static int backward_impl(const alif_desc *desc, const alif_params *prm, const vo
         a.gI = grad_current;
         a.gI16 = gi16 ? reinterpret_cast<uint16_t *>((char *)workspace + lay.gi16) : nullptr;
         a.part = part;
-        if (bwd_streams(desc, p, grad_current != nullptr, gi16, grad_v || grad_theta, max_bytes)) {
-            a.chunks = bwd_stream_chunks(p.B, p.T, p.N, p.TR, max_bytes);
+        if (bwd_streams(desc, p, grad_current != nullptr, gi16, grad_v || grad_theta)) {
+            a.chunks = bwd_stream_chunks(p.B, p.T, p.N, p.TR);
             e = launch_bwd_stream(a, st);
         } else {
             e = launch_blocks_bwd(a, st);
@@ -555,19 +552,6 @@ static int backward_impl(const alif_desc *desc, const alif_params *prm, const vo
     return ALIF_OK;
 }
 
-extern "C" {
-
-int alif_backward(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
-                  const float *current, const void *carries, const float *grad_spikes,
-                  const float *grad_v, const float *grad_theta, float *grad_current,
-                  float *grad_input, float *grad_W, float *grad_bias, float *grad_tau_mem,
-                  float *grad_tau_adapt, float *grad_d, float *grad_theta0, void *workspace,
-                  void *stream) {
-    return backward_impl(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
-                         grad_input, grad_W, grad_bias, grad_tau_mem, grad_tau_adapt, grad_d, grad_theta0,
-                         workspace, stream, SIZE_MAX);
-}
-
 int alif_backward_noalloc(const alif_desc *desc, const alif_params *prm, const void *input, const float *W,
                           const float *current, const void *carries, const float *grad_spikes,
                           const float *grad_v, const float *grad_theta, float *grad_current,
@@ -592,10 +576,9 @@ int alif_backward_noalloc(const alif_desc *desc, const alif_params *prm, const v
     if ((rc = noalloc_scratch(&ws))) return rc;
     // every scratch byte the kernels read they have written earlier in the same call
     // (the partial sums of every (b, neuron), every split's tile), so nothing is cleared
-    // (the streaming backward takes one chunk where more would not fit the array)
-    return backward_impl(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
+    return alif_backward(desc, prm, input, W, current, carries, grad_spikes, grad_v, grad_theta, grad_current,
                          grad_input, grad_W, grad_bias, grad_tau_mem, grad_tau_adapt, grad_d, grad_theta0, ws,
-                         stream, ALIF_NOALLOC_SCRATCH_BYTES);
+                         stream);
 }
 
 // ---------------------------------------------------------------------------

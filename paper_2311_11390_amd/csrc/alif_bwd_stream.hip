@@ -17,7 +17,8 @@
 // and a the forward saved at its first block, with W = U = Q = 0, and also sums
 //   CB = sum src pv,  CA = sum lt pa,  pv = prod beta (1 - S),  pa = p^steps,
 // the weights its sums have on the W, U and Q that reach it; k_join_chunks joins the
-// chunks in time order. Spike steps come from the saved carries, as in the block
+// chunks in time order. A chunk keeps ten doubles a neuron: whether it holds a reset
+// (pv = 0, else beta^steps) is the sign of U, which is never negative. Spike steps come from the saved carries, as in the block
 // backward; the state between them is recomputed here.
 //
 // Everything but the surrogate is FP64: on this machine an FP64 multiply-add issues at
@@ -30,6 +31,7 @@
 // and the batch sum: 64 x 256 x 20000, T_R 40: 611 -> 524 (5.0 TB/s); 4 x 2048 x 20000,
 // T_R 20: 888 -> 268 (4.9 TB/s); 8 x 600 x 10000, T_R 100: 606 -> 124; 16 x 256 x 2000,
 // T_R 2: 349 -> 44.
+#include "../../include/blockalif.h"
 #include "alif_common.h"
 #include "alif_kernels.h"
 
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
 
     if (n < N) {
         const size_t BN = (size_t)a.B * N, S = a.chunks * BN;
-        double *o = a.part + (a.chunks > 1 ? 5 * BN : 0) + (size_t)ch * BN + (size_t)b * N + n;
+        double *o = a.part + (size_t)ch * BN + (size_t)b * N + n;
         o[0] = sb;
         o[S] = dd * sp;
         o[2 * S] = sd;
@@ -242,11 +244,9 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
         if (a.chunks > 1) {
             o[5 * S] = CB;
             o[6 * S] = dd * CA;
-            o[7 * S] = pv;
-            o[8 * S] = pa;
-            o[9 * S] = W;
-            o[10 * S] = U;
-            o[11 * S] = Q;
+            o[7 * S] = W;
+            o[8 * S] = pv == 0.0 ? -U : U;
+            o[9 * S] = Q;
         }
     }
 }
@@ -254,8 +254,9 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
 // The chunks' sums of one (b, n) joined in time order: the W, U and Q that reach a chunk
 // are those of the chunks before it, decayed by its pv and pa. Two neighbouring chunks
 // make one of the same form (Part::then), so JG threads compose a share of the chunks each
-// and one adds the shares up through LDS: 250 chunks of a single row take 31 loads in
-// sequence instead of 250. k_finalize then sums over the batch.
+// and one adds the shares up through LDS: the 64 chunks of a single row take 8 loads in
+// sequence instead of 64. The joined sums go over the first chunks' (a column's are read
+// and written by one workgroup). k_finalize then sums over the batch.
 constexpr int JG = 8;
 
 struct Part {
@@ -277,20 +278,26 @@ struct Part {
     }
 };
 
-__global__ __launch_bounds__(64 * JG) void k_join_chunks(size_t BN, int chunks, const double *__restrict__ in,
-                                                         double *__restrict__ out) {
+__global__ __launch_bounds__(64 * JG) void k_join_chunks(BwdArgs a) {
     __shared__ double sh[JG][12][64];
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const size_t i = (size_t)blockIdx.x * 64 + l, S = (size_t)chunks * BN;
-    const int per = (chunks + JG - 1) / JG, c1 = min(chunks, (g + 1) * per);
+    const size_t BN = (size_t)a.B * a.N, i = (size_t)blockIdx.x * 64 + l, S = (size_t)a.chunks * BN;
+    const int per = (a.chunks + JG - 1) / JG, c1 = min(a.chunks, (g + 1) * per);
     Part t{0, 0, 0, 0, 0, 0, 0, 1, 1, 0, 0, 0};   // no step
-    if (i < BN)
+    if (i < BN) {
+        const int n = (int)(i % a.N), steps = a.nbc * a.TR;
+        const double lb = -a.dt / (double)a.tau_m[n], lp = -a.dt / (double)a.tau_a[n];
+        const double pv = exp(lb * steps), pa = exp(lp * steps);   // over a whole chunk without a reset
+        const double last = (double)(a.T - (a.chunks - 1) * steps), pvl = exp(lb * last), pal = exp(lp * last);
 #pragma unroll 2
         for (int c = g * per; c < c1; c++) {
-            const double *q = in + (size_t)c * BN + i;
-            t.then(Part{q[0], q[S], q[2 * S], q[3 * S], q[4 * S], q[5 * S], q[6 * S], q[7 * S], q[8 * S], q[9 * S],
-                        q[10 * S], q[11 * S]});
+            const double *q = a.part + (size_t)c * BN + i;
+            const double u = q[8 * S];
+            const bool end = c == a.chunks - 1;
+            t.then(Part{q[0], q[S], q[2 * S], q[3 * S], q[4 * S], q[5 * S], q[6 * S],
+                        signbit(u) ? 0.0 : end ? pvl : pv, end ? pal : pa, q[7 * S], fabs(u), q[9 * S]});
         }
+    }
     double *o = &sh[g][0][l];
     o[0] = t.b; o[64] = t.p; o[128] = t.d; o[192] = t.th; o[256] = t.bias; o[320] = t.CB;
     o[384] = t.CA; o[448] = t.pv; o[512] = t.pa; o[576] = t.W; o[640] = t.U; o[704] = t.Q;
@@ -300,17 +307,19 @@ __global__ __launch_bounds__(64 * JG) void k_join_chunks(size_t BN, int chunks, 
         const double *q = &sh[h][0][l];
         t.then(Part{q[0], q[64], q[128], q[192], q[256], q[320], q[384], q[448], q[512], q[576], q[640], q[704]});
     }
-    out[i] = t.b;
-    out[BN + i] = t.p;
-    out[2 * BN + i] = t.d;
-    out[3 * BN + i] = t.th;
-    out[4 * BN + i] = t.bias;
+    double *out = a.part + i;
+    out[0] = t.b;
+    out[BN] = t.p;
+    out[2 * BN] = t.d;
+    out[3 * BN] = t.th;
+    out[4 * BN] = t.bias;
 }
 
 // The input-current gradient from the src a forward pass left in its place: the adjoint
 // of the membrane, backward in time over the same chunks,
 //   lam[t] = src[t] + nu[t+1],  nu[t] = beta (1 - S[t-1]) lam[t],  gI[t] = (1 - beta) gate[t] lam[t],
-// with the nu that reaches a chunk composed from the CB and pv of the chunks behind it.
+// with the nu that reaches a chunk composed from the CB and pv of the chunks behind it
+// (those between it and the last are whole).
 // Six vector instructions a step, in FP64 but for src (the FP32 value the block backward
 // sums) and gI. What bounds it: HBM, a read and a write a step.
 template <int KS, int TRS>
@@ -331,10 +340,13 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_gi_reverse(BwdArgs a) {
     const double beta = exp(-dt / tm), omb = -expm1(-dt / tm);
     const size_t BN = (size_t)a.B * N, S = a.chunks * BN, TN = (size_t)a.T * N, CN = (size_t)(a.NB + 1) * N;
     double nu = 0.0;
-    {
-        const double *q = a.part + 5 * BN + (size_t)b * N + nc;
+    if (ch < a.chunks - 1) {   // uniform
+        const double *q = a.part + (size_t)b * N + nc;
+        const double pv = exp(-dt / tm * (double)(a.nbc * TR));
+        nu = q[5 * S + (a.chunks - 1) * BN];
 #pragma unroll 4
-        for (int c = a.chunks - 1; c > ch; c--) nu = fma(q[7 * S + c * BN], nu, q[5 * S + c * BN]);
+        for (int c = a.chunks - 2; c > ch; c--)
+            nu = fma(signbit(q[8 * S + c * BN]) ? 0.0 : pv, nu, q[5 * S + c * BN]);
     }
 
     struct Slot {
@@ -446,10 +458,10 @@ void stream_launch(const BwdArgs &a, unsigned grid, hipStream_t st) {
 }  // namespace
 
 size_t bwd_stream_bytes(int B, int N, int chunks) {
-    return (size_t)(chunks > 1 ? 5 + 12 * (size_t)chunks : 5) * B * N * sizeof(double);
+    return (size_t)(chunks > 1 ? 10 * chunks : 5) * B * N * sizeof(double);
 }
 
-int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
+int bwd_stream_chunks(int B, int T, int N, int TR) {
     const long long waves = (long long)B * ((N + 63) / 64);
     if (waves == 0 || T == 0) return 1;
     const int NB = (T + TR - 1) / TR;
@@ -457,9 +469,13 @@ int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
     c = c < T / ST_MIN_STEPS ? c : T / ST_MIN_STEPS;
     c = c < NB ? c : NB;
     c = c < ST_MAX_CHUNKS ? c : ST_MAX_CHUNKS;
+    // as many as fit the static scratch, whichever scratch the call has: the sums, and so the
+    // bits, do not depend on it (the waves aimed at fit but for counts that round up far)
+    const long long fit = (long long)ALIF_NOALLOC_SCRATCH_BYTES / (long long)(bwd_stream_bytes(B, N, 2) / 2);
+    c = c < fit ? c : fit;
     if (c <= 1) return 1;
-    const int nbc = (int)((NB + c - 1) / c), chunks = (NB + nbc - 1) / nbc;   // every chunk holds a block
-    return bwd_stream_bytes(B, N, chunks) <= max_bytes ? chunks : 1;
+    const int nbc = (int)((NB + c - 1) / c);
+    return (NB + nbc - 1) / nbc;   // every chunk holds a block
 }
 
 // Whether a backward that wants dL/dI streams. The block backward runs a row's blocks in
@@ -472,9 +488,8 @@ int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes) {
 // steps that the block ends inside (and 16 with dL/dV or dL/dtheta) does not fit the block
 // kernel's registers, where streaming wins throughout: T_R 50: 129 / 67 (8 x 1000 x 1024),
 // 706 / 299 (64 x 1000 x 1024); T_R 100: 1334 / 551 (128 x 1000 x 1024).
-bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt, size_t max_bytes) {
+bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt) {
     const BlockConfig c = block_config(TR);
-    if (bwd_stream_chunks(B, T, N, TR, max_bytes) < bwd_stream_chunks(B, T, N, TR, SIZE_MAX)) return false;
     if (c.seg == 8 && ((c.len >= 8 && TR != c.seg * c.len) || (gvt && c.len == 16))) return true;
     const double steps = (double)B * T * N * 1e-6, NB = (T + TR - 1) / TR;
     const double serial = 10.0 + NB * (c.seg == 1 ? 0.26 + 0.05 * TR : 0.6 + 0.02 * TR);
@@ -502,11 +517,8 @@ hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {
         else if (ks == 6) stream_launch<6, 0>(a, grid, st);
         else stream_launch<5, 0>(a, grid, st);
     }
-    if (a.chunks > 1) {
-        const size_t BN = (size_t)a.B * a.N;
-        hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)((BN + 63) / 64)), dim3(64 * JG), 0, st, BN, a.chunks,
-                           (const double *)(a.part + 5 * BN), a.part);
-    }
+    if (a.chunks > 1)
+        hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)(((size_t)a.B * a.N + 63) / 64)), dim3(64 * JG), 0, st, a);
     return hipGetLastError();
 }
 

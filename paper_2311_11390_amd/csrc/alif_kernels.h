@@ -61,7 +61,7 @@ struct BwdArgs {
     float *gI;
     uint16_t *gI16;  // the same gradient as bfloat16 (round to nearest even), in place of gI
                      // (detached policy, no gV / gTH); nullptr: none
-    double *part;  // [5][B][N]; the streaming backward with chunks > 1 keeps [12][chunks][B][N] behind it
+    double *part;  // [5][B][N]; the streaming backward's chunks (> 1) leave [10][chunks][B][N] there first
     int chunks, nbc;  // streaming backward: time chunks a row, blocks a chunk (nbc set by its launch)
 };
 
@@ -199,12 +199,12 @@ hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st);
 hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 // The detached backward as passes over time chunks (alif_bwd_stream.hip): the
-// time chunks a row is cut into (1 when their sums would pass max_bytes), the bytes of
+// time chunks a row is cut into (their sums fit ALIF_NOALLOC_SCRATCH_BYTES), the bytes of
 // `part` for that many, and the kernel (with the join of the chunks' sums).
-int bwd_stream_chunks(int B, int T, int N, int TR, size_t max_bytes);
+int bwd_stream_chunks(int B, int T, int N, int TR);
 size_t bwd_stream_bytes(int B, int N, int chunks);
 // whether it takes a call with one (float gI)
-bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt, size_t max_bytes);
+bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt);
 hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st);
 hipError_t launch_decay_tables(int N, int TR, double dt, const float *tau_m, const float *tau_a,
                                float *beta_pow, float *p_pow, hipStream_t st);

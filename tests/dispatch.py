@@ -5,19 +5,24 @@ import ctypes
 
 from paper_2311_11390_amd import _lib as L
 
-_SIZE_MAX = ctypes.c_size_t(-1).value
-
 
 def streams_dI(B, T, N, TR, gvt=False) -> bool:
     """Whether the detached backward with a float dL/dI streams over time chunks
     (``gvt``: with dL/dV or dL/dtheta); else it is the block kernel."""
-    f = getattr(L.load(), "_ZN4alif13bwd_stream_giEiiiibm")
-    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 4 + [ctypes.c_bool, ctypes.c_size_t]
-    return f(B, T, N, TR, gvt, _SIZE_MAX)
+    f = getattr(L.load(), "_ZN4alif13bwd_stream_giEiiiib")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 4 + [ctypes.c_bool]
+    return f(B, T, N, TR, gvt)
 
 
 def stream_chunks(B, T, N, TR) -> int:
     """Time chunks a row of the streaming backward is cut into."""
-    f = getattr(L.load(), "_ZN4alif17bwd_stream_chunksEiiiim")
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_size_t]
-    return f(B, T, N, TR, _SIZE_MAX)
+    f = getattr(L.load(), "_ZN4alif17bwd_stream_chunksEiiii")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4
+    return f(B, T, N, TR)
+
+
+def stream_bytes(B, N, chunks) -> int:
+    """Scratch of that many chunks' sums."""
+    f = getattr(L.load(), "_ZN4alif16bwd_stream_bytesEiii")
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int] * 3
+    return f(B, N, chunks)
