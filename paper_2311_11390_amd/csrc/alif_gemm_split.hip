@@ -1,24 +1,24 @@
 // FP32 GEMM on the bfloat16 matrix cores (gfx950): the float operands of the Eq. 3
 // projections are cut into three bfloat16 pieces while they are staged,
-//   v = h + m + l,  h = v's upper 16 bits, m = bf16(v - h), l = v - h - m,
-// which together hold all 24 bits of v, and every product of pieces that reaches
-// 2^-24 of the result is accumulated in FP32:
+//   v = h + m + l,  h = bf16(v), m = bf16(v - h), l = v - h - m (each rounded to nearest),
+// which together hold all 24 bits of v (|m| <= 2^-8, |l| <= 2^-17 of v's binade), and the
+// products of pieces are accumulated in FP32:
 //   spikes x float   (uint8 and bfloat16 spikes are one piece): x h, x m, x l;
-//   float x float    h h, h m, m h, m m, h l, l h (what is left out is below 2^-23 of a
-//                    product and of either sign).
+//   float x float    all but l l, which is below 2^-33 of a product. (Without m l and l m
+//                    a single product was off by up to 2^-24 more than its rounding.)
 // Products of bfloat16 are exact in FP32, and h h is accumulated apart from the rest: sums
 // of 8-bit (16-bit) numbers are exact or nearly so, and the rest is 2^-7 of them and less.
-// So the error against 64 bits is below that of a plain FP32 GEMM (relative 2-norm, 32000
-// x 700 x 512, 2.5% active: current 2.7e-8 against 3.4e-8, dW 1.23e-7 against 1.48e-7, dx
-// 1.3e-7 against 4.1e-7; with one accumulator for both dW had 1.52e-7).
+// So the error against 64 bits is that of FP32 multiply-adds for sums of one or two terms and
+// below it for longer ones (relative 2-norm, 32000 x 700 x 512, 2.5% active, a plain FP32 GEMM
+// / this one: current 8.2e-8 / 2.5e-8, dW 1.48e-7 / 9.1e-8, dx 4.0e-7 / 1.27e-7).
 //
 // Why: v_mfma_f32_32x32x16_bf16 multiplies 16 times as fast as v_mfma_f32_16x16x4_f32,
-// so three or six of them still beat it. us, FP32 kernel -> this one: 32000 x 700 x 512
-// current 217 -> 99, dW 262 -> 117, dx 258 -> 185; 65536 x 512 x 512 311 -> 150, 321 ->
-// 153, 337 -> 262; 131072 x 200 x 256 156 -> 98, 188 -> 95, 196 -> 152; never slower down
-// to 1200 x 64 x 64. The matrix cores are busy 28-39% of that time; the conversions (5.5
-// vector instructions an element and plane triple) and the LDS round trip of the pieces
-// take the rest.
+// so three or eight of them still beat it. us, FP32 kernel -> this one (uint8 spikes): 32000 x
+// 700 x 512 current 196 -> 91, dW 239 -> 91, dx 228 -> 192; 65536 x 512 x 512 289 -> 141, 310 ->
+// 130, 301 -> 270; 64000 x 200 x 256 79 -> 50, 107 -> 51, 91 -> 82; 1200 x 64 x 64 15.3 -> 13.3,
+// 37 -> 23, 15.6 -> 15.2. The matrix cores are busy 28% (current), 36% (dW) and 46% (dx) of that
+// time; the conversions (5.5 vector instructions an element and plane triple) and the LDS round
+// trip of the pieces take the rest. m l and l m cost dx 13-15% (65536 x 512 x 512 235 without).
 //
 // Range. A tile whose float operands hold an infinity or a magnitude from 2^60 up
 // (where a piece could overflow apart from the others, or 0 x inf turn up between pieces)
@@ -28,8 +28,8 @@
 //
 // Tiling. 256 threads own 128 x 128 of C, each wave 64 x 64 as 2 x 2 accumulators of
 // v_mfma_f32_32x32x16_bf16. K moves through two LDS buffers in stages of 32 (four
-// planes) or 16 (six planes), 64 KiB and two workgroups a CU, 24 MFMAs a wave between
-// barriers.
+// planes) or 16 (six planes), 64 KiB and two workgroups a CU, 24 or 32 MFMAs a wave
+// between barriers.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -77,9 +77,8 @@ constexpr int buf_elems(int planes) { return (planes * BK + 63) / 64 * (ST * 64)
 
 // two floats as three packed pairs of bfloat16
 __device__ __forceinline__ void split2(float v0, float v1, uint32_t &h, uint32_t &m, uint32_t &l) {
-    const uint32_t b0 = __float_as_uint(v0), b1 = __float_as_uint(v1);
-    h = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-    const float r0 = v0 - __uint_as_float(b0 & 0xffff0000u), r1 = v1 - __uint_as_float(b1 & 0xffff0000u);
+    h = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v0, (__bf16)v1});
+    const float r0 = v0 - __uint_as_float(h << 16), r1 = v1 - __uint_as_float(h & 0xffff0000u);
     m = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)r0, (__bf16)r1});
     const float l0 = r0 - __uint_as_float(m << 16), l1 = r1 - __uint_as_float(m & 0xffff0000u);
     l = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);   // exact
@@ -281,17 +280,17 @@ __global__ __launch_bounds__(NT, 2) void k_gemm_split(GemmArgs g, int m_tiles, i
                 c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[p][i], fb[q][j], c, 0, 0, 0);
             }
     };
-    // the products of one k16 step, in two halves
+    // the products of one k16 step, the smallest first, in two halves (three products: one)
     auto mul_half = [&](int half) __attribute__((always_inline)) {
         int n = 0;
 #pragma unroll
-        for (int o = 2; o >= 0; o--)
+        for (int o = 3; o >= 0; o--)
 #pragma unroll
             for (int p = 0; p < NA; p++)
 #pragma unroll
                 for (int q = 0; q < NB; q++) {
                     if (p + q != o) continue;
-                    if (n++ < 3 ? half == 0 : half == 1) mul(p, q);
+                    if (n++ < 4 ? half == 0 : half == 1) mul(p, q);
                 }
     };
 
