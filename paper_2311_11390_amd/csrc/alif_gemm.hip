@@ -815,13 +815,15 @@ hipError_t gemm_input_current(size_t M, int N, int K, GemmIn x, const float *W, 
     return gemm_launch(g, bf16, st);
 }
 
-// K splits of the weight gradient: workgroups for the card, each at least 256 rows deep. FP32:
-// two a CU (which its LDS allows at a time); four measured 159 against 138 us at 65536 x 512 x 512
-// and 123 against 102 us at 32000 x 700 x 512, one 151 and 121 us. Fewer partial sums also
-// leave a smaller error (1.5e-7 against 1.1e-7).
-static int wgrad_splits(size_t M, int N, int K, bool bf16) {
+// K splits of the weight gradient: `workgroups` for the card, each at least 256 rows deep. FP32
+// on the bfloat16 matrix cores: 512, two a CU (which its LDS allows at a time); 1024 measured 159
+// against 138 us at 65536 x 512 x 512 and 123 against 102 us at 32000 x 700 x 512, 256 151 and
+// 121 us, and fewer partial sums also leave a smaller error (1.5e-7 against 1.1e-7). The other
+// kernels: 1024 (odd widths on the general kernel, 16000 x 1001 x 1001 956 us against 978 with
+// 512, 32000 x 700 x 513 990 against 967).
+static int wgrad_splits(size_t M, int N, int K, int workgroups) {
     const long long tiles = (long long)((N + GBN - 1) / GBN) * ((K + GBM - 1) / GBM);
-    long long s = (bf16 ? 1024 : 512) / (tiles > 0 ? tiles : 1);
+    long long s = workgroups / (tiles > 0 ? tiles : 1);
     s = s < 1 ? 1 : (s > 64 ? 64 : s);
     const long long maxs = (long long)M / 256;
     if (s > maxs) s = maxs < 1 ? 1 : maxs;
@@ -829,7 +831,7 @@ static int wgrad_splits(size_t M, int N, int K, bool bf16) {
 }
 
 size_t gemm_workspace_bytes(size_t M, int N, int K) {
-    const int s = wgrad_splits(M, N, K, true);
+    const int s = wgrad_splits(M, N, K, 1024);
     return s > 1 ? (size_t)s * N * K * sizeof(float) : 0;
 }
 
@@ -842,7 +844,8 @@ hipError_t gemm_weight_grad(size_t M, int N, int K, const void *gI, GemmIn x, fl
     g.A = gI; g.a_dt = gi_bf16 ? 2 : 0; g.lda = N; g.a_kc = 0;
     g.B = x.ptr; g.b_dt = dt_of(x.kind); g.ldb = K; g.b_kc = 0;
     g.C = gW; g.ldc = K; g.bias = nullptr;
-    g.splits = wgrad_splits(M, N, K, bf16);
+    g.splits = wgrad_splits(M, N, K, 512);
+    if (bf16 || !gemm_split_ok(g)) g.splits = wgrad_splits(M, N, K, 1024);
     g.C_part = (float *)ws;
     g.skip_cnt = skip_cnt;
     g.skip_le = skip_le;
