@@ -69,7 +69,7 @@ ALIF_CONFIGS(ALIF_EXTERN)
 
 hipError_t launch_blocks_fwd(const FwdArgs &a, hipStream_t st) {
     BlockConfig c = block_config(a.TR);
-    if (fwd_chain_ok(a.B, a.N, a.TR, a.V || a.TH, a.ck.v != nullptr)) return launch_fwd_chain(a, st);
+    if (fwd_chain_ok(a.B, a.N, a.TR, a.NB, a.V || a.TH, a.ck.v != nullptr)) return launch_fwd_chain(a, st);
 #define ALIF_F(S, L) if (c.seg == S && c.len == L) return blocks_fwd_launch<S, L>(a, st);
     ALIF_CONFIGS(ALIF_F)
 #undef ALIF_F

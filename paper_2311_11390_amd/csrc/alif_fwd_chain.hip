@@ -328,9 +328,13 @@ __global__ __launch_bounds__(256) void k_fwd_chain(FwdArgs a) {
 // write rows in wider pieces. us, block kernel / this one: T_R 2: 768 groups 118 / 121 with
 // carries, 107 / 65 without; 1024 groups 138 / 165 and 112 / 70; T_R 20 without: 640 groups 55 / 42,
 // 1024 groups 77 / 74; T_R 28: 512 groups 48 / 37, 640 groups 61 / 69.
-bool fwd_chain_ok(int B, int N, int TR, bool traces, bool carries) {
+// A call of one block (the recurrent layer over 256 neurons makes one a block) has no chain, but
+// its loads and stores still run beside each other: 8 x 320, with carries, T_R 2 6.2 / 5.5, 4 8.3 /
+// 5.6, 10 6.1 / 5.5, 20 8.2 / 7.9, 32 11.3 / 11.2; T_R 3, whose groups of 16 blocks are the
+// longest to load, 6.9 / 7.0 (32 x 1024: 7.3 / 7.7), and from four blocks on 7.6 / 7.1.
+bool fwd_chain_ok(int B, int N, int TR, int NB, bool traces, bool carries) {
     const int most = TR > 24 ? 512 : carries ? 640 : TR == 3 ? 768 : 1024;
-    return TR <= 32 && !traces && (long long)B * ((N + 63) / 64) <= most;
+    return TR <= 32 && !traces && (TR != 3 || NB >= 4) && (long long)B * ((N + 63) / 64) <= most;
 }
 
 hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st) {

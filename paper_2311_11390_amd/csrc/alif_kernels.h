@@ -194,7 +194,7 @@ hipError_t launch_transpose(int N, const float *in, float *out, hipStream_t st);
 hipError_t launch_shift_time(int B, int T, int N, int D, int elem, const void *in, void *out, hipStream_t st,
                              const unsigned long long *skip_cnt = nullptr, unsigned long long skip_le = 0);
 // the forward without traces where the card is not full (alif_fwd_chain.hip): same bits; which calls
-bool fwd_chain_ok(int B, int N, int TR, bool traces, bool carries);
+bool fwd_chain_ok(int B, int N, int TR, int NB, bool traces, bool carries);
 hipError_t launch_fwd_chain(FwdArgs a, hipStream_t st);
 hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);

@@ -26,3 +26,11 @@ def stream_bytes(B, N, chunks) -> int:
     f = getattr(L.load(), "_ZN4alif16bwd_stream_bytesEiii")
     f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int] * 3
     return f(B, N, chunks)
+
+
+def forward_chains(B, N, TR, NB, traces=False, carries=False) -> bool:
+    """Whether the forward runs the recurrence on a wave of its own (k_fwd_chain); else
+    it is the block kernel."""
+    f = getattr(L.load(), "_ZN4alif12fwd_chain_okEiiiibb")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
+    return f(B, N, TR, NB, traces, carries)
