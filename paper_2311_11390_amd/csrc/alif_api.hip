@@ -473,6 +473,13 @@ int alif_backward(const alif_desc *desc, const alif_params *prm, const void *inp
     double *part = (double *)workspace;
 
     hipError_t e;
+    FinalizeArgs f{};
+    f.B = p.B; f.N = p.N; f.dt = desc->dt_ms;
+    f.tau_m = prm->tau_mem_ms; f.tau_a = prm->tau_adapt_ms;
+    f.part = part;
+    f.g_tau_m = grad_tau_mem; f.g_tau_a = grad_tau_adapt; f.g_d = grad_d; f.g_theta0 = grad_theta0;
+    f.g_bias = grad_bias;
+    bool streamed = false;   // (its launch ends with the sums over the batch)
     if (desc->algo == ALIF_ALGO_BLOCKS) {
         BwdArgs a{};
         a.B = p.B; a.T = p.T; a.N = p.N; a.TR = p.TR; a.NB = p.NB;
@@ -490,9 +497,10 @@ int alif_backward(const alif_desc *desc, const alif_params *prm, const void *inp
         a.gI = grad_current;
         a.gI16 = gi16 ? reinterpret_cast<uint16_t *>((char *)workspace + lay.gi16) : nullptr;
         a.part = part;
-        if (bwd_streams(desc, p, grad_current != nullptr, gi16, grad_v || grad_theta)) {
+        streamed = bwd_streams(desc, p, grad_current != nullptr, gi16, grad_v || grad_theta);
+        if (streamed) {
             a.chunks = bwd_stream_chunks(p.B, p.T, p.N, p.TR);
-            e = launch_bwd_stream(a, st);
+            e = launch_bwd_stream(a, f, st);
         } else {
             e = launch_blocks_bwd(a, st);
         }
@@ -514,14 +522,10 @@ int alif_backward(const alif_desc *desc, const alif_params *prm, const void *inp
         e = launch_seq_bwd(a, st);
         if (e != hipSuccess) return hip_fail(e, "sequential backward launch");
     }
-    FinalizeArgs f{};
-    f.B = p.B; f.N = p.N; f.dt = desc->dt_ms;
-    f.tau_m = prm->tau_mem_ms; f.tau_a = prm->tau_adapt_ms;
-    f.part = part;
-    f.g_tau_m = grad_tau_mem; f.g_tau_a = grad_tau_adapt; f.g_d = grad_d; f.g_theta0 = grad_theta0;
-    f.g_bias = grad_bias;
-    e = launch_finalize(f, st);
-    if (e != hipSuccess) return hip_fail(e, "gradient finalize launch");
+    if (!streamed) {
+        e = launch_finalize(f, st);
+        if (e != hipSuccess) return hip_fail(e, "gradient finalize launch");
+    }
 
     if (p.spikes_in) {
         GemmIn in;

@@ -35,13 +35,7 @@ __global__ __launch_bounds__(64 * FIN_PH) void k_finalize(FinalizeArgs a) {
         for (int k = 0; k < FIN_PH; k++) t += red[k][q][nl];
         s[q] = t;
     }
-    const double tm = a.tau_m[n], ta = a.tau_a[n];
-    const double beta = exp(-a.dt / tm), p = exp(-a.dt / ta);
-    if (a.g_tau_m) a.g_tau_m[n] = (float)(s[0] * beta * a.dt / (tm * tm));
-    if (a.g_tau_a) a.g_tau_a[n] = (float)(s[1] * p * a.dt / (ta * ta));
-    if (a.g_d) a.g_d[n] = (float)s[2];
-    if (a.g_theta0) a.g_theta0[n] = (float)s[3];
-    if (a.g_bias) a.g_bias[n] = (float)s[4];
+    finalize_neuron(a, n, s);
 }
 
 __global__ void k_decay_tables(int N, int TR, double dt, const float *tau_m, const float *tau_a,

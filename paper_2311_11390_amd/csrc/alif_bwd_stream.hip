@@ -28,9 +28,10 @@
 // What bounds it: HBM. A quiet step is 26 vector instructions and no barrier or LDS (the
 // block backward issues 51 and stitches segments behind a barrier a block, on one
 // wave-group per 64 neurons whatever T is). Against that kernel, us a call with the join
-// and the batch sum: 64 x 256 x 20000, T_R 40: 611 -> 524 (5.0 TB/s); 4 x 2048 x 20000,
-// T_R 20: 888 -> 268 (4.9 TB/s); 8 x 600 x 10000, T_R 100: 606 -> 124; 16 x 256 x 2000,
-// T_R 2: 349 -> 44.
+// and the batch sum: 64 x 256 x 20000, T_R 40: 605 -> 520 (5.0 TB/s; 550 right after a
+// forward, when the clock is lower); 4 x 2048 x 20000, T_R 20: 888 -> 272 (4.8 TB/s); 8 x 600 x
+// 10000, T_R 100: 606 -> 124; 16 x 256 x 2000, T_R 2: 349 -> 44. Short calls are bound by a chunk's
+// latency, some 0.17 us a step: over 500 calls of 250 to 8000 steps none measured slower.
 #include "../../include/blockalif.h"
 #include "alif_common.h"
 #include "alif_kernels.h"
@@ -40,12 +41,9 @@ namespace {
 
 constexpr int ST_WAVES = 4;   // waves (work items) a workgroup
 constexpr int ST_FAR = 1 << 30;
-// Waves the chunks aim at. Against 1024 / 2048 / 4096 / 8192 waves, 3072 (three a SIMD)
-// measured 524 us on 64 x 256 x 20000 steps at T_R 40 (595 / 540 / 544 / 569: below, too
-// little in flight; above, more streams over memory and more sums to join) and 268 us on
-// 4 x 2048 x 20000 at T_R 20 (354 / 278 / 282 / 310).
-constexpr int ST_TARGET_WAVES = 3072;
-constexpr int ST_MIN_STEPS = 64;   // a chunk's set-up (five exponentials, a first load) is worth about 16 steps
+constexpr int ST_SIMDS = 1024;   // 256 CUs
+constexpr int ST_MOST = 4;       // waves a SIMD that the chunks aim at, at most
+constexpr int ST_MIN_STEPS = 24;   // a chunk's set-up (five exponentials, a first load) is worth about 16 steps
 constexpr int ST_MAX_CHUNKS = 64;  // the join walks an eighth of them in sequence, 1.4 us each
 constexpr int ST_RING = 2;         // groups of steps in registers; 3 measured the same
 
@@ -278,41 +276,94 @@ struct Part {
     }
 };
 
+// Composes the chunks [c0, c1) of column i ([10][chunks][B][N] in a.part).
+__device__ __forceinline__ Part compose(const BwdArgs &a, size_t i, int c0, int c1) {
+    Part t{0, 0, 0, 0, 0, 0, 0, 1, 1, 0, 0, 0};   // no step
+    const size_t BN = (size_t)a.B * a.N, S = (size_t)a.chunks * BN;
+    const int n = (int)(i % a.N), steps = a.nbc * a.TR;
+    const double lb = -a.dt / (double)a.tau_m[n], lp = -a.dt / (double)a.tau_a[n];
+    const double pv = exp(lb * steps), pa = exp(lp * steps);   // over a whole chunk without a reset
+    const double last = (double)(a.T - (a.chunks - 1) * steps), pvl = exp(lb * last), pal = exp(lp * last);
+#pragma unroll 2
+    for (int c = c0; c < c1; c++) {
+        const double *q = a.part + (size_t)c * BN + i;
+        const double u = q[8 * S];
+        const bool end = c == a.chunks - 1;
+        t.then(Part{q[0], q[S], q[2 * S], q[3 * S], q[4 * S], q[5 * S], q[6 * S],
+                    signbit(u) ? 0.0 : end ? pvl : pv, end ? pal : pa, q[7 * S], fabs(u), q[9 * S]});
+    }
+    return t;
+}
+template <int W>
+__device__ __forceinline__ void put_part(double *o, const Part &t) {
+    o[0] = t.b; o[W] = t.p; o[2 * W] = t.d; o[3 * W] = t.th; o[4 * W] = t.bias; o[5 * W] = t.CB;
+    o[6 * W] = t.CA; o[7 * W] = t.pv; o[8 * W] = t.pa; o[9 * W] = t.W; o[10 * W] = t.U; o[11 * W] = t.Q;
+}
+template <int W>
+__device__ __forceinline__ Part get_part(const double *q) {
+    return Part{q[0], q[W], q[2 * W], q[3 * W], q[4 * W], q[5 * W], q[6 * W], q[7 * W], q[8 * W], q[9 * W], q[10 * W], q[11 * W]};
+}
+
 __global__ __launch_bounds__(64 * JG) void k_join_chunks(BwdArgs a) {
     __shared__ double sh[JG][12][64];
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const size_t BN = (size_t)a.B * a.N, i = (size_t)blockIdx.x * 64 + l, S = (size_t)a.chunks * BN;
-    const int per = (a.chunks + JG - 1) / JG, c1 = min(a.chunks, (g + 1) * per);
-    Part t{0, 0, 0, 0, 0, 0, 0, 1, 1, 0, 0, 0};   // no step
-    if (i < BN) {
-        const int n = (int)(i % a.N), steps = a.nbc * a.TR;
-        const double lb = -a.dt / (double)a.tau_m[n], lp = -a.dt / (double)a.tau_a[n];
-        const double pv = exp(lb * steps), pa = exp(lp * steps);   // over a whole chunk without a reset
-        const double last = (double)(a.T - (a.chunks - 1) * steps), pvl = exp(lb * last), pal = exp(lp * last);
-#pragma unroll 2
-        for (int c = g * per; c < c1; c++) {
-            const double *q = a.part + (size_t)c * BN + i;
-            const double u = q[8 * S];
-            const bool end = c == a.chunks - 1;
-            t.then(Part{q[0], q[S], q[2 * S], q[3 * S], q[4 * S], q[5 * S], q[6 * S],
-                        signbit(u) ? 0.0 : end ? pvl : pv, end ? pal : pa, q[7 * S], fabs(u), q[9 * S]});
-        }
-    }
-    double *o = &sh[g][0][l];
-    o[0] = t.b; o[64] = t.p; o[128] = t.d; o[192] = t.th; o[256] = t.bias; o[320] = t.CB;
-    o[384] = t.CA; o[448] = t.pv; o[512] = t.pa; o[576] = t.W; o[640] = t.U; o[704] = t.Q;
+    const size_t BN = (size_t)a.B * a.N, i = (size_t)blockIdx.x * 64 + l;
+    const int per = (a.chunks + JG - 1) / JG;
+    Part t{0, 0, 0, 0, 0, 0, 0, 1, 1, 0, 0, 0};
+    if (i < BN) t = compose(a, i, g * per, min(a.chunks, (g + 1) * per));
+    put_part<64>(&sh[g][0][l], t);
     __syncthreads();
     if (g != 0 || i >= BN) return;
-    for (int h = 1; h < JG; h++) {
-        const double *q = &sh[h][0][l];
-        t.then(Part{q[0], q[64], q[128], q[192], q[256], q[320], q[384], q[448], q[512], q[576], q[640], q[704]});
-    }
+    for (int h = 1; h < JG; h++) t.then(get_part<64>(&sh[h][0][l]));
     double *out = a.part + i;
     out[0] = t.b;
     out[BN] = t.p;
     out[2 * BN] = t.d;
     out[3 * BN] = t.th;
     out[4 * BN] = t.bias;
+}
+
+// Few sums: the join and k_finalize in one launch, 32 neurons a workgroup on JP threads each,
+// which share out the batch elements and, below JP of those, an element's chunks.
+constexpr int JP = 16, JC = 32;
+
+__host__ __device__ constexpr int join_shares(int B) {   // threads an element
+    int s = 1;
+    while (2 * s * B <= JP) s *= 2;
+    return s;
+}
+
+__global__ __launch_bounds__(JP * JC) void k_join_finalize(BwdArgs a, FinalizeArgs f) {
+    __shared__ double sh[JP][12][JC];
+    const int l = threadIdx.x % JC, ph = threadIdx.x / JC, n = blockIdx.x * JC + l;
+    const int S = join_shares(a.B), share = ph % S, per = (a.chunks + S - 1) / S;
+    double s[5] = {0, 0, 0, 0, 0};
+    if (n < a.N)
+        for (int b = ph / S; b < a.B; b += JP / S) {   // (S > 1: one element at most)
+            const Part t = compose(a, (size_t)b * a.N + n, share * per, min(a.chunks, (share + 1) * per));
+            if (S > 1) put_part<JC>(&sh[ph][0][l], t);
+            s[0] += t.b; s[1] += t.p; s[2] += t.d; s[3] += t.th; s[4] += t.bias;
+        }
+    if (S > 1) {   // uniform
+        __syncthreads();
+        if (share == 0 && ph / S < a.B && n < a.N) {
+            Part t = get_part<JC>(&sh[ph][0][l]);
+            for (int h = 1; h < S; h++) t.then(get_part<JC>(&sh[ph + h][0][l]));
+            s[0] = t.b; s[1] = t.p; s[2] = t.d; s[3] = t.th; s[4] = t.bias;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < 5; q++) sh[ph][q][l] = s[q];
+    __syncthreads();
+    if (ph != 0 || n >= a.N) return;
+#pragma unroll
+    for (int q = 0; q < 5; q++) {
+        double t = 0.0;
+        for (int k = 0; k < JP; k += S) t += sh[k][q][l];
+        s[q] = t;
+    }
+    finalize_neuron(f, n, s);
 }
 
 // The input-current gradient from the src a forward pass left in its place: the adjoint
@@ -461,47 +512,69 @@ size_t bwd_stream_bytes(int B, int N, int chunks) {
     return (size_t)(chunks > 1 ? 10 * chunks : 5) * B * N * sizeof(double);
 }
 
+// The SIMDs work through waves of equal length, so a row cut into c chunks takes as long as the
+// SIMD with the most of them: ceil(c waves / 1024) times a chunk's steps and set-up, somewhat
+// more where one or two waves leave a SIMD's latency open. The least of that over the counts
+// that give a SIMD at most four waves, a chunk a block and 24 steps, and whose sums fit
+// the static scratch (whichever scratch a call has, so the bits do not depend on it). us, with
+// the join: 64 x 256 x 20000 at T_R 40 by chunks 6 / 8 / 9 / 12 / 13 / 16 / 24: 565 / 525 / 591 /
+// 518 / 587 / 546 / 541; 19 x 773 x 13195, T_R 64, 8 / 9 / 12 / 13 / 16: 339 / 406 / 356 / 395 / 348;
+// 119 x 77 x 2008, T_R 120 (17 blocks), 9 / 17: 78 / 57.
 int bwd_stream_chunks(int B, int T, int N, int TR) {
     const long long waves = (long long)B * ((N + 63) / 64);
     if (waves == 0 || T == 0) return 1;
     const int NB = (T + TR - 1) / TR;
-    long long c = (ST_TARGET_WAVES + waves - 1) / waves;
-    c = c < T / ST_MIN_STEPS ? c : T / ST_MIN_STEPS;
-    c = c < NB ? c : NB;
-    c = c < ST_MAX_CHUNKS ? c : ST_MAX_CHUNKS;
-    // as many as fit the static scratch, whichever scratch the call has: the sums, and so the
-    // bits, do not depend on it (the waves aimed at fit but for counts that round up far)
+    long long most = (T + ST_MIN_STEPS - 1) / ST_MIN_STEPS;
+    most = most < NB ? most : NB;
+    most = most < ST_MAX_CHUNKS ? most : ST_MAX_CHUNKS;
     const long long fit = (long long)ALIF_NOALLOC_SCRATCH_BYTES / (long long)(bwd_stream_bytes(B, N, 2) / 2);
-    c = c < fit ? c : fit;
-    if (c <= 1) return 1;
-    const int nbc = (int)((NB + c - 1) / c);
-    return (NB + nbc - 1) / nbc;   // every chunk holds a block
+    most = most < fit ? most : fit;
+    int best = 1;
+    double least = 0.0;
+    for (int c = 1; c <= most; c++) {
+        const int nbc = (NB + c - 1) / c;
+        if (c > 1 && ((NB + nbc - 1) / nbc != c || c * waves > (long long)ST_MOST * ST_SIMDS)) continue;
+        const long long deep = (c * waves + ST_SIMDS - 1) / ST_SIMDS;
+        const double cost = (double)deep * ((double)nbc * TR + 16.0) * (deep == 1 ? 1.3 : deep == 2 ? 1.07 : 1.0);
+        if (c == 1 || cost < least) {
+            best = c;
+            least = cost;
+        }
+    }
+    return best;
 }
 
 // Whether a backward that wants dL/dI streams. The block backward runs a row's blocks in
 // sequence, 64 to 256 neurons a workgroup, so a call that does not fill the card takes its
-// blocks times c(T_R) us; else it moves 12 bytes a step. Streaming cuts time as well, but moves
-// 20 bytes a step (the source written and read), after 35 us of launches, set-up and join.
-// Measured, us, block / streaming: T_R 2: 32 x 1000 x 512 209 / 80, 64 x 1000 x 512 221 / 149,
-// 64 x 1000 x 1024 247 / 293; T_R 10: 64 x 4000 x 256 339 / 294, 64 x 1000 x 512 125 / 153;
-// T_R 40: 16 x 20000 x 128 574 / 199, 32 x 1000 x 512 56 / 88. A segment of more than eight
-// steps that the block ends inside (and 16 with dL/dV or dL/dtheta) does not fit the block
-// kernel's registers, where streaming wins throughout: T_R 50: 129 / 67 (8 x 1000 x 1024),
-// 706 / 299 (64 x 1000 x 1024); T_R 100: 1334 / 551 (128 x 1000 x 1024).
+// blocks times c(T_R) us; else it moves 12 bytes a step. Streaming takes its set-up, launches
+// and join, 0.3 us a step of a chunk in both directions, 0.2 us a chunk composed on the way
+// back, and moves 20 bytes a step (the source written and read). Over 500 calls (T_R 2 to 128, 1 to
+// 128 rows of 250 to 8000 steps, 20 to 1024 neurons) it never took the slower one. us, block /
+// streaming: T_R 2: 32 x 1000 x 512 209 / 80, 64 x 1000 x 512 221 / 149, 64 x 1000 x 1024 247 / 293;
+// T_R 10: 64 x 4000 x 256 339 / 294, 64 x 1000 x 512 125 / 153; T_R 40: 16 x 20000 x 128 574 / 199,
+// 32 x 1000 x 512 56 / 88; T_R 64: 11 x 1149 x 45 50 / 54 with the chunks of 128 steps this took before.
+// A segment of more than eight steps that the block ends inside (and 16 with dL/dV or dL/dtheta)
+// does not fit the block kernel's registers, where streaming wins from four blocks on: T_R 50:
+// 129 / 67 (8 x 1000 x 1024), 706 / 299 (64 x 1000 x 1024); T_R 100: 1334 / 551 (128 x 1000 x 1024), but 43 / 45
+// (70 x 287 x 28, three blocks).
 bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt) {
     const BlockConfig c = block_config(TR);
-    if (c.seg == 8 && ((c.len >= 8 && TR != c.seg * c.len) || (gvt && c.len == 16))) return true;
-    const double steps = (double)B * T * N * 1e-6, NB = (T + TR - 1) / TR;
+    const int NB = (T + TR - 1) / TR;
+    if (NB > 3 && c.seg == 8 && ((c.len >= 8 && TR != c.seg * c.len) || (gvt && c.len == 16))) return true;
+    const double steps = (double)B * T * N * 1e-6;
     const double serial = 10.0 + NB * (c.seg == 1 ? 0.26 + 0.05 * TR : 0.6 + 0.02 * TR);
-    const double moved = 2.9 * steps * (gvt ? 20.0 / 12 : 1.0), stream = 35.0 + 4.2 * steps * (gvt ? 28.0 / 20 : 1.0);
+    const int chunks = bwd_stream_chunks(B, T, N, TR);
+    const double L = (double)((NB + chunks - 1) / chunks) * TR;
+    const double moved = 2.9 * steps * (gvt ? 20.0 / 12 : 1.0);
+    const double stream = 14.0 + 0.3 * L + 0.2 * chunks + 4.2 * steps * (gvt ? 28.0 / 20 : 1.0);
     return stream < (serial > moved ? serial : moved);
 }
 
-hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {
+hipError_t launch_bwd_stream(BwdArgs a, const FinalizeArgs &f, hipStream_t st) {
     a.nbc = (a.NB + a.chunks - 1) / a.chunks;
     a.n_groups = (a.N + 63) / 64;
     const long long items = (long long)a.B * a.chunks * a.n_groups;
-    if (items == 0) return hipSuccess;
+    if (items == 0) return launch_finalize(f, st);
     const unsigned grid = (unsigned)((items + ST_WAVES - 1) / ST_WAVES);
     if (a.TR == 2) stream_launch<8, 2>(a, grid, st);
     else if (a.TR == 3) stream_launch<6, 3>(a, grid, st);
@@ -517,9 +590,17 @@ hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st) {
         else if (ks == 6) stream_launch<6, 0>(a, grid, st);
         else stream_launch<5, 0>(a, grid, st);
     }
+    // us a call, join and k_finalize / one launch: 1 x 100, 8 chunks 20.4 / 19.2, 64 chunks 31.6 / 23.8;
+    // 2 x 1024, 8 chunks 21.1 / 20.2; 4 x 100, 16 chunks 23.2 / 23.2; 8 x 100, 16 chunks 23.7 / 26.3
+    // (fewer threads an element). A launch less for the host, too.
+    if (a.chunks > 1 && a.B <= 4) {
+        hipLaunchKernelGGL(k_join_finalize, dim3((unsigned)((a.N + JC - 1) / JC)), dim3(JP * JC), 0, st, a, f);
+        return hipGetLastError();
+    }
     if (a.chunks > 1)
         hipLaunchKernelGGL(k_join_chunks, dim3((unsigned)(((size_t)a.B * a.N + 63) / 64)), dim3(64 * JG), 0, st, a);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_finalize(f, st) : e;
 }
 
 }  // namespace alif

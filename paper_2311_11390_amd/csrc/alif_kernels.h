@@ -128,6 +128,16 @@ struct FinalizeArgs {
     const double *part;  // [5][B][N]
     float *g_tau_m, *g_tau_a, *g_d, *g_theta0, *g_bias;
 };
+// the gradients of neuron n from its sums s[5] (d beta, d p, d d, d theta0, d bias)
+__device__ __forceinline__ void finalize_neuron(const FinalizeArgs &a, int n, const double (&s)[5]) {
+    const double tm = a.tau_m[n], ta = a.tau_a[n];
+    const double beta = exp(-a.dt / tm), p = exp(-a.dt / ta);
+    if (a.g_tau_m) a.g_tau_m[n] = (float)(s[0] * beta * a.dt / (tm * tm));
+    if (a.g_tau_a) a.g_tau_a[n] = (float)(s[1] * p * a.dt / (ta * ta));
+    if (a.g_d) a.g_d[n] = (float)s[2];
+    if (a.g_theta0) a.g_theta0[n] = (float)s[3];
+    if (a.g_bias) a.g_bias[n] = (float)s[4];
+}
 
 // (SEG, L) segmentation of a block of T_R steps over lanes; same for fwd and bwd.
 struct BlockConfig {
@@ -200,12 +210,12 @@ hipError_t launch_blocks_bwd(const BwdArgs &a, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 // The detached backward as passes over time chunks (alif_bwd_stream.hip): the
 // time chunks a row is cut into (their sums fit ALIF_NOALLOC_SCRATCH_BYTES), the bytes of
-// `part` for that many, and the kernel (with the join of the chunks' sums).
+// `part` for that many, and the kernels, through the sums over chunks and batch.
 int bwd_stream_chunks(int B, int T, int N, int TR);
 size_t bwd_stream_bytes(int B, int N, int chunks);
 // whether it takes a call with one (float gI)
 bool bwd_stream_gi(int B, int T, int N, int TR, bool gvt);
-hipError_t launch_bwd_stream(BwdArgs a, hipStream_t st);
+hipError_t launch_bwd_stream(BwdArgs a, const FinalizeArgs &f, hipStream_t st);
 hipError_t launch_decay_tables(int N, int TR, double dt, const float *tau_m, const float *tau_a,
                                float *beta_pow, float *p_pow, hipStream_t st);
 
