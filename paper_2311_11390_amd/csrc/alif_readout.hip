@@ -147,8 +147,10 @@ __global__ __launch_bounds__(RTH) void k_readout_bwd(int B, int T, int C, int CG
     const float *ir = Ir + base, *vr = Vr + base;
     float *gi = gIr + base;
     // the carry at this chunk's end: lambda at step t1 from the T - t1 steps of the later
-    // chunks, g (1 + beta + ... + beta^(T - t1 - 1))
-    double lam = omb > 0.0 ? g * (-expm1(lb * (double)(T - t1)) / omb) : g * (double)(T - t1);
+    // chunks, g (1 + beta + ... + beta^(T - t1 - 1)); none without later steps (0 times an infinite
+    // g or an infinite rate is not)
+    double lam = 0.0;
+    if (t1 < T) lam = omb != 0.0 ? g * (-expm1(lb * (double)(T - t1)) / omb) : g * (double)(T - t1);
     double gb = 0.0;
     for (int tb = t1 - 1; tb >= t0; tb -= RUB) {
         float xi[RUB], xv[RUB];
