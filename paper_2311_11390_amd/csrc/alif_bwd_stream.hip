@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     const int N = a.N, TR = TRS > 0 ? TRS : a.TR;
     const int n = g * 64 + lane, nc = min(n, N - 1);
     const int blk0 = ch * a.nbc, blk1 = min(a.NB, blk0 + a.nbc);
-    const int tend = min(a.T, blk1 * TR);
+    const int tbeg = blk0 * TR, tend = min(a.T, blk1 * TR);
 
     const double dt = a.dt, tm = a.tau_m[nc], ta = a.tau_a[nc];
     const double beta = exp(-dt / tm), omb = -expm1(-dt / tm), p = exp(-dt / ta);
@@ -130,7 +130,8 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
     };
 
     // the local terms of step t0 + k, once V, a and the sensitivities are its own
-    auto collect = [&](const Slot &s, int k, int t0) __attribute__((always_inline)) {
+    // (a masked step's U is zero; its source may be infinite)
+    auto collect = [&](const Slot &s, int k, int t0, bool gate) __attribute__((always_inline)) {
         const double u = V - fma(dd, av, th0);
         const float gs = (!GVT && !GI) || hasS ? s.gs[k] : 0.0f;
         const double q = (double)(gs * surrogate_grad<SG>((float)u, a.slope));
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
             lt = hasT ? (double)s.gt[k] - q : -q;
         }
         sb = fma(src, W, sb);
-        sbias = fma(src, U, sbias);
+        sbias = gate ? fma(src, U, sbias) : sbias;
         sp = fma(lt, Q, sp);
         sd = fma(lt, av, sd);
         sth += lt;
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
                 av *= p;
                 pv *= beta;
                 pa *= p;
-                collect(s, k, t0);
+                collect(s, k, t0, true);
             }
         } else {
 #pragma unroll
@@ -187,15 +188,15 @@ __global__ __launch_bounds__(64 * ST_WAVES) void k_bwd_stream(BwdArgs a) {
                     const bool spv = t - 1 == tl, gate = t - tl >= TR;
                     const double x = gate ? (double)s.x[k] + bias : 0.0;
                     const double Wn = fma(beta, W, V - x), Vn = fma(beta, V, omb * x);
-                    const double Un = fma(beta, U, gate ? omb : 0.0);
                     W = spv ? 0.0 : Wn;
-                    V = spv ? 0.0 : Vn;
-                    U = spv ? 0.0 : Un;
+                    // (the carry has the reset of a spike before the chunk; an initial state may hold any V)
+                    V = spv && (k > 0 || t0 != tbeg) ? 0.0 : Vn;
+                    U = gate ? fma(beta, U, omb) : 0.0;   // (zero from the reset to the gate's opening)
                     pv = spv ? 0.0 : pv * beta;
                     Q = fma(p, Q, av);
                     av = fma(p, av, spv ? 1.0 : 0.0);
                     pa *= p;
-                    collect(s, k, t0);
+                    collect(s, k, t0, gate);
                 }
         }
         const int cl = tc[M - 1];
@@ -265,7 +266,7 @@ struct Part {
         p += fma(x.CA, Q, x.p);
         d += x.d;
         th += x.th;
-        bias += fma(x.CB, U, x.bias);
+        bias += U != 0.0 ? fma(x.CB, U, x.bias) : x.bias;   // (x.CB may be infinite)
         CB = fma(x.CB, pv, CB);
         CA = fma(x.CA, pa, CA);
         W = fma(x.pv, W, x.W);
