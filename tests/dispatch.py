@@ -1,8 +1,12 @@
 """The library's own dispatch rules, for tests that have to reach one kernel. They are
 plain host functions of the library (C++, hence the mangled names), so a test that
-names a path fails when a rule moves it to another."""
+names a path fails when a rule moves it to another.
+
+torch is imported first: the library binds to the HIP runtime that torch brings only if
+that one is loaded, and a process with two of them dies at its first GPU call."""
 import ctypes
 
+import torch  # noqa: F401
 from paper_2311_11390_amd import _lib as L
 
 

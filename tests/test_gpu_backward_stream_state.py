@@ -4,7 +4,7 @@ where its rule keeps the block kernel; the path is asserted)."""
 import numpy as np
 import pytest
 
-from dispatch import streams_dI
+from dispatch import stream_chunks, streams_dI
 from gpu_helpers import driven_current, gpu_forward, log, np_, random_params
 from parity import check_grad
 from paper_2311_11390_amd.synth import rng
@@ -65,3 +65,21 @@ def test_bias_gradient_beside_infinite_gradients_of_masked_steps(TR, bad):
         np.testing.assert_array_equal(np.isfinite(a[k]), np.isfinite(b[k]), err_msg=k)
         ok = np.isfinite(b[k])
         check_grad(k, a[k][ok], b[k][ok])
+
+
+@pytest.mark.parametrize("TR,T", [(2, 201), (5, 203), (20, 410), (40, 803)])
+def test_resumed_run_in_several_chunks(TR, T):
+    """A run resumed from a saved state (live masks, adaptation), cut into chunks, against the
+    block backward on the same piece."""
+    import torch
+    B, N = 128, 512
+    assert stream_chunks(B, T, N, TR) > 1
+    log(f"[stream state] resumed T_R={TR} T={T}")
+    I = driven_current(940 + TR, B, 10 * TR, N)
+    prm = random_params(940 + TR, N, tm=(2.0, 30.0), bias=(-0.3, 0.3))
+    f, _, _ = gpu_forward(I, prm, 2.0 / TR, 2.0, traces=False, want_final=True)
+    assert (f["final"]["ts"] > 1).any() and (f["final"]["a"] > 0).any()
+    gS = rng(941 + TR).standard_normal((B, T, N)).astype(np.float32)
+    a, b = _both(B, T, N, TR, 940 + TR, f["final"], gS)
+    for k in _ALL:
+        check_grad(k, a[k], b[k])
