@@ -505,6 +505,12 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_slice(RecArgs a) {
 #pragma unroll
     for (int i = 0; i < DEPTH; i++) load(buf[i], a.nb0 + i);
 
+    // The recurrent sums of the next block: in LDS rows that only steps with an event touch, or, where
+    // a neuron's one wave has few steps, in registers with more events in flight (60 Hz, 64 x 128: T_R 2
+    // 1.21 -> 0.99, T_R 4 1.10 -> 1.00 of one launch's time; T_R 4 at 256 neurons, 8 and 16 got slower).
+    constexpr bool REG = L <= 2 || (SEG == 1 && NG == 2);
+    constexpr int EV = 4;
+    float accr[REG ? L : 1];
     uint32_t hit = 0;   // steps of this segment with a recurrent term (wave-uniform)
     const int qD = (D + TR - 1) / TR;   // source blocks lie qD or qD - 1 blocks back
 
@@ -512,6 +518,9 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_slice(RecArgs a) {
     // its LDS words tsp, older ones from the ring).
     auto gather = [&](int nt, const int *tsp) __attribute__((always_inline)) {
         hit = 0;
+        if constexpr (REG)
+#pragma unroll
+            for (int k = 0; k < L; k++) accr[k] = 0.0f;
 #pragma unroll 1
         for (int q = 0; q < 2; q++) {
             const int m = nt - qD + q;   // uniform
@@ -536,7 +545,30 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_slice(RecArgs a) {
             for (int g = 0; g < NG; g++) {
                 const int t = tsj[g], r = base + t;
                 uint64_t mk = __ballot(t > 0 && g * 64 + lane < N && r >= c.t0 && r < r_end);
-                while (mk) {   // two events at a time: their loads are in flight together
+                if constexpr (REG) {
+                    while (mk) {   // EV events at a time: their loads are in flight together
+                        int kk[EV];
+                        float w[EV];
+#pragma unroll
+                        for (int e = 0; e < EV; e++) {
+                            kk[e] = -1;
+                            w[e] = 0.0f;
+                            if (mk) {
+                                const int l = __builtin_ctzll(mk);
+                                mk &= mk - 1;
+                                kk[e] = __builtin_amdgcn_readlane(r, l) - c.t0;
+                                w[e] = ld_f32(rW, (uint32_t)(g * 64 + l) * wrow + wcol);
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < EV; e++) {
+#pragma unroll
+                            for (int k = 0; k < L; k++) accr[k] = k == kk[e] ? accr[k] + w[e] : accr[k];
+                            hit |= kk[e] >= 0 ? 1u << kk[e] : 0u;
+                        }
+                    }
+                }
+                while (!REG && mk) {   // two events at a time: their loads are in flight together
                     const int l0 = __builtin_ctzll(mk);
                     mk &= mk - 1;
                     const bool two = mk != 0;
@@ -565,7 +597,7 @@ __global__ __launch_bounds__(64 * NG * SEG) void k_recurrent_slice(RecArgs a) {
         if (hit) {   // uniform
 #pragma unroll
             for (int k = 0; k < L; k++)
-                if ((hit >> k) & 1u) bi[k] += acc[k * 64];
+                if ((hit >> k) & 1u) bi[k] += REG ? accr[REG ? k : 0] : acc[k * 64];
         }
         const float cv = (float)v0d, ca = (float)a0d;
         const int mpre = cts > 0 ? cts - 1 : 0;
@@ -656,11 +688,18 @@ inline int rec_slices(double bytes, int NB) {
 // Which runs go in slices. They save a chain about 0.1 ns a step and neuron and cost the run
 // some 50 us (two more launches, the last slice's expansion): forward, us, one launch / slices:
 // 64 x 1000 x 256 182 / 200, 64 x 2500 x 128 284 / 293, 64 x 4000 x 128 442 / 440, 32 x 4000 x 256
-// 495 / 413, 64 x 15000 x 64 816 / 558. Rows that do not align four neurons expand at a quarter of
-// the rate, which many of them beside the chain do not hide: 32 x 2000 x 255 264 / 288, 32 x 8000 x 255
-// 974 / 802, 64 x 8000 x 201 955 / 1161.
-inline bool rec_sliced(int B, int T, int N, bool vec4) {
-    return (long long)T * N >= (vec4 ? 500000 : 800000) && (vec4 || (long long)B * N <= 8192);
+// 495 / 413, 64 x 15000 x 64 816 / 558.
+// Spikes cost them more: the expansion gathers the rows of W_rec^T once again, beside the chain.
+// Slices' time over one launch's with no spikes / at 6 / 15 / 60 Hz (ARP 2 ms, T 10000): 64 x 256: T_R 2
+// 0.74 / 0.96 / 0.98 / 1.00, 4 0.87 / 0.99 / 1.02 / 1.06, 8 0.83 / 1.00 / 1.00 / 1.05, 10 0.85 / 0.97 / 0.94 /
+// 0.93, 40 0.63 / 0.73 / 0.75 / 0.79; 64 x 128: T_R 2 0.81 / 0.94 / 0.96 / 0.99, 10 0.91 / 1.03 / 1.08 / 1.22, 16
+// 0.95 / 1.01 / 1.06 / 1.18, 20 0.80 / 0.89 / 0.96 / 1.07, 40 0.68 / 0.86 / 0.94 / 0.96; 16 x 128, where more CUs
+// expand: T_R 10 0.84 / 0.93 / 0.96 / 1.06, 16 0.85 / 0.91 / 0.93 / 1.02. So they are taken where 15 Hz do not
+// make them slower. Rows that do not align four neurons expand at a quarter of the rate, which many
+// of them beside the chain do not hide: 32 x 127, T_R 24: 0.74 / 0.83 / 0.91 / 1.03; 64 x 127: 0.81 / 1.18 / 1.27 / 1.30.
+inline bool rec_sliced(int B, int T, int N, int TR, bool vec4) {
+    const bool spikes_ok = B <= 16 || (N <= 128 ? TR <= 4 || TR >= 20 : TR <= 2 || TR >= 8);
+    return spikes_ok && (long long)T * N >= (vec4 ? 500000 : 800000) && (vec4 || (long long)B * N <= 4096);
 }
 
 // W_rec transposed, and pd[n][k] = p^k in FP64, k < T_R: the values of the block forward's table
@@ -683,7 +722,7 @@ hipError_t recurrent_fused_launch(RecArgs a, hipStream_t st) {
     a.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.I) | reinterpret_cast<uintptr_t>(a.I_ff)) & 15) == 0 &&
              (reinterpret_cast<uintptr_t>(a.spikes) & (4 * sb - 1)) == 0;
     const bool tr = a.V || a.TH;
-    if (tr || !rec_sliced(a.B, a.T, a.N, a.vec4)) {
+    if (tr || !rec_sliced(a.B, a.T, a.N, a.TR, a.vec4)) {
         const size_t base = rec_smem_fixed<SEG, NG>(a.TR) + (size_t)a.ring * 64 * NG;
         const size_t smc = rec_stage_offset(base) + rec_stage_bytes<SEG, L, NG>();
         // chunked stores: whole 16-neuron chunks in every row and room for the staging tile
